@@ -305,6 +305,14 @@ struct EpiArgs {
 size_t gemm_workspace_bytes(int kind, int P, int Q, int R, int conv = 0);
 hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, void* ws,
                        hipStream_t stream);
+// The fp32 contractions that run on the bf16 matrix cores (exact three-way
+// operand splits); tile, splits and workspace are gemm_launch's choice.
+hipError_t split_launch_linear(int kind, int tile, int S, int cz, int r_split, const GemmProblem& pr,
+                               const EpiArgs& ea, void* ws, int vec_ops, int vec_epi,
+                               hipStream_t stream);
+hipError_t split_launch_conv(int kind, int tile, int S, int cz, int r_split, const GemmProblem& pr,
+                             const EpiArgs& ea, void* ws, int vec_ops, int vec_epi,
+                             hipStream_t stream);
 // bf16-operand contractions (operands rounded to bf16, fp32 accumulation);
 // kinds EPI_FWD, EPI_DGRAD, EPI_WGRAD, EPI_WGRAD_BF; strided operands only.
 size_t gemm_bf16_workspace_bytes(int kind, int P, int Q, int R);

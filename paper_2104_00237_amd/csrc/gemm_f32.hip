@@ -1,6 +1,11 @@
 // fp32 MFMA contractions of a linear layer, with the optimizer fused into
 // their prologue (forward-fusion) or epilogue (backward-fusion).
 //
+// This file chooses the tiling of every fp32 contraction and holds the kernels
+// for the small and the narrow ones, which latency or memory bound; products
+// that the fp32 matrix rate would bound run on the bf16 matrix cores with split
+// operands (gemm_split.h).
+//
 // One tiled kernel computes C[P,Q] = sum_r A(p,r) B(q,r) on the CDNA matrix
 // cores (v_mfma_f32_32x32x2_f32).  A workgroup of 4 wavefronts owns a BP x BQ
 // output tile; wavefronts split it WP x WQ and, when WR > 1, also split each
@@ -40,7 +45,7 @@
 #include <cstdio>
 #include <cstdlib>
 
-#include "gemm_common.h"
+#include "gemm_tiles.h"
 
 namespace opfuse {
 
@@ -77,246 +82,19 @@ using T64x64 = Tile<64, 64, 16, 2, 2, 1, 4>;
 using T128x64 = Tile<128, 64, 16, 2, 2, 1, 4>;
 using T128x128 = Tile<128, 128, 16, 2, 2, 1, 3>;
 using T256x32 = Tile<256, 32, 16, 4, 1, 1, 3>;
-// 64 rows x 128 columns with the reduction layout of T64x32 (32-deep chunks,
-// each halved between two wavefronts): every output element takes the same
-// MFMA sequence as on T64x32, so results are identical to it bit for bit.
-using T64x128 = Tile<64, 128, 32, 1, 2, 2, 4, 2>;
 
 // TI_32x32D, TI_32x32D8: 32x32 blocks with operands loaded straight into the
 // matrix-core registers by 4 or 8 wavefronts (gemm_direct_kernel; forward and
 // data gradient of linear layers only, the LDS-staged 32x32 tile elsewhere).
 enum TileId {
   TI_32x32 = 0, TI_64x32, TI_64x64, TI_128x64, TI_128x128, TI_256x32,
-  TI_32x32D, TI_32x32D8, TI_64x128, TI_COUNT
+  TI_32x32D, TI_32x32D8,
+  TI_S128x128, TI_S64x128, TI_S64x64, TI_S64x32, TI_COUNT
 };
-static const int kTileBP[TI_COUNT] = {32, 64, 64, 128, 128, 256, 32, 32, 64};
-static const int kTileBQ[TI_COUNT] = {32, 32, 64, 64, 128, 32, 32, 32, 128};
-static const int kTileBR[TI_COUNT] = {32, 32, 16, 16, 16, 16, 32, 32, 32};
+static const int kTileBP[TI_COUNT] = {32, 64, 64, 128, 128, 256, 32, 32, 128, 64, 64, 64};
+static const int kTileBQ[TI_COUNT] = {32, 32, 64, 64, 128, 32, 32, 32, 128, 128, 64, 32};
+static const int kTileBR[TI_COUNT] = {32, 32, 16, 16, 16, 16, 32, 32, 16, 32, 32, 32};
 
-
-// A BX (output dim) x BR (reduction) tile of one operand, held in registers as
-// float4s between its global load and its LDS store.  RC: the reduction index
-// is contiguous in memory (else the output index is).  `base` points at the
-// tile's first element; nx / nr are the valid extents from there (<= 0: none).
-// vec: 128-bit loads (base 16B aligned, strides and both extents' ends
-// multiples of 4 along the contiguous index).
-template <int BX, int BR, bool RC, bool VEC, int PAD = 4>
-struct TileLoad {
-  static constexpr int NV = BX * BR / 4;
-  static constexpr int PER = (NV + 255) / 256;
-  float4 v[PER];
-
-  __device__ __forceinline__ void load(const float* tensor, const GemmProblem&, int64_t s_x,
-                                       int64_t s_r, int x0, int r0, int nx, int nr, int tid) {
-    const rsrc_t rs = make_rsrc(tensor + (int64_t)x0 * s_x + (int64_t)r0 * s_r);
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = tid + i * 256;
-      int x, r;
-      if (RC) { x = idx / (BR / 4); r = (idx % (BR / 4)) * 4; }
-      else    { r = idx / (BX / 4); x = (idx % (BX / 4)) * 4; }
-      const bool live = NV % 256 == 0 || idx < NV;
-      if constexpr (VEC) {
-        const bool ok = live && x < nx && r < nr;
-        const uint32_t off = ok ? (uint32_t)((x * s_x + r * s_r) * 4) : kOOB;
-        v[i] = bload4(rs, off);
-      } else {
-        float e[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int xx = RC ? x : x + k, rr = RC ? r + k : r;
-          const bool ok = live && xx < nx && rr < nr;
-          e[k] = bload1(rs, ok ? (uint32_t)((xx * s_x + rr * s_r) * 4) : kOOB);
-        }
-        v[i] = make_float4(e[0], e[1], e[2], e[3]);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(float* lds, int tid) const {
-    constexpr int LD = BX + PAD;
-    static_assert(RC || PAD % 4 == 0, "float4 stores need 16-byte aligned rows");
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = tid + i * 256;
-      if (NV % 256 == 0 || idx < NV) {
-        if (RC) {
-          const int x = idx / (BR / 4), r = (idx % (BR / 4)) * 4;
-          lds[(r + 0) * LD + x] = v[i].x;
-          lds[(r + 1) * LD + x] = v[i].y;
-          lds[(r + 2) * LD + x] = v[i].z;
-          lds[(r + 3) * LD + x] = v[i].w;
-        } else {
-          const int r = idx / (BX / 4), x = (idx % (BX / 4)) * 4;
-          *reinterpret_cast<float4*>(&lds[r * LD + x]) = v[i];
-        }
-      }
-    }
-  }
-};
-
-// Convolution operands gathered from NHWC tensors / KRSC filters.  Element
-// (x, r) of the tile is tensor element (x0 + x, r0 + r) of the implicit GEMM
-// operand; its offset is formed from the convolution geometry, and elements in
-// the zero padding (or past the operand) read from an out-of-range offset.
-// VEC: the channel count along the contiguous index is a multiple of 4, so a
-// float4 never straddles two filter taps.
-enum GatherKind { G_FWD_A = 1, G_DGRAD_A = 2, G_WGRAD_B = 3, G_DGRAD_B = 4 };
-
-template <int KIND>
-__device__ __forceinline__ int64_t gather_off(const GemmProblem& g, int x, int r, bool& ok) {
-  // FWD_A: x = m, r = k = (tap, c).  DGRAD_A: x = m, r = k = (tap, co).
-  // WGRAD_B: x = k = (tap, c), r = m.  DGRAD_B: x = c, r = k = (tap, co).
-  if constexpr (KIND == G_DGRAD_B) {
-    const int tap = fdiv(r, g.dCout), co = r - tap * g.cCout;
-    return ((int64_t)co * 9 + tap) * g.cC + x;
-  } else {
-    const int m = (KIND == G_WGRAD_B) ? r : x;
-    const int k = (KIND == G_WGRAD_B) ? x : r;
-    const int ch = (KIND == G_DGRAD_A) ? g.cCout : g.cC;
-    const FastDiv& fch = (KIND == G_DGRAD_A) ? g.dCout : g.dC;
-    const int t = fdiv(m, g.dW), w = m - t * g.cW;
-    const int n = fdiv(t, g.dH), h = t - n * g.cH;
-    const int tap = fdiv(k, fch), c = k - tap * ch;
-    const int rr = tap / 3, ss = tap - 3 * rr;
-    const int hi = (KIND == G_DGRAD_A) ? h + 1 - rr : h + rr - 1;
-    const int wi = (KIND == G_DGRAD_A) ? w + 1 - ss : w + ss - 1;
-    ok = ok && hi >= 0 && hi < g.cH && wi >= 0 && wi < g.cW;
-    return (((int64_t)n * g.cH + hi) * g.cW + wi) * ch + c;
-  }
-}
-
-template <int BX, int BR, bool RC, bool VEC, int KIND>
-struct GatherLoad : TileLoad<BX, BR, RC, VEC> {
-  using Base = TileLoad<BX, BR, RC, VEC>;
-  using Base::v;
-  __device__ __forceinline__ void load(const float* tensor, const GemmProblem& g, int64_t, int64_t,
-                                       int x0, int r0, int nx, int nr, int tid) {
-    const rsrc_t rs = make_rsrc(tensor);
-#pragma unroll
-    for (int i = 0; i < Base::PER; ++i) {
-      const int idx = tid + i * 256;
-      int x, r;
-      if (RC) { x = idx / (BR / 4); r = (idx % (BR / 4)) * 4; }
-      else    { r = idx / (BX / 4); x = (idx % (BX / 4)) * 4; }
-      const bool live = idx < Base::NV;
-      if constexpr (VEC) {
-        bool ok = live && x < nx && r < nr;
-        const int64_t o = gather_off<KIND>(g, x0 + x, r0 + r, ok);
-        v[i] = bload4(rs, ok ? (uint32_t)(o * 4) : kOOB);
-      } else {
-        float e[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int xx = RC ? x : x + k, rr = RC ? r + k : r;
-          bool ok = live && xx < nx && rr < nr;
-          const int64_t o = gather_off<KIND>(g, x0 + xx, r0 + rr, ok);
-          e[k] = bload1(rs, ok ? (uint32_t)(o * 4) : kOOB);
-        }
-        v[i] = make_float4(e[0], e[1], e[2], e[3]);
-      }
-    }
-  }
-};
-
-// Forward-fusion B operand: W tile (reduction-contiguous) with its pending
-// update.  load() issues the loads of W, g, m, v; apply() runs after the
-// previous chunk's MFMAs, updates, writes back and stages the new W in LDS.
-// `off` is relative to the tile's first element (row stride ldw).
-template <int BX, int BR, bool VEC>
-struct FFTileLoad {
-  static constexpr int NV = BX * BR / 4;
-  static constexpr int PER = (NV + 255) / 256;
-  float4 w[PER], g[PER], m[PER], v[PER];
-  int valid[PER];  // bit e set: element e of the float4 is inside the matrix
-  int64_t base;    // element index of the tile origin in W
-
-  __device__ __forceinline__ void load(const EpiArgs& ea, int64_t ldw, int x0, int r0, int nx,
-                                       int nr, int tid) {
-    const bool adam = ea.opt.kind != OF_OPT_SGD;
-    base = (int64_t)x0 * ldw + r0;
-    const rsrc_t rw = make_rsrc(ea.W.w + base), rg = make_rsrc(ea.gW + base);
-    const rsrc_t rm = make_rsrc_opt(ea.W.m, base);
-    const rsrc_t rv = adam ? make_rsrc(ea.W.v + base) : rm;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = tid + i * 256;
-      const int x = idx / (BR / 4), r = (idx % (BR / 4)) * 4;
-      const bool live = idx < NV && x < nx;
-      if constexpr (VEC) {
-        const bool ok = live && r < nr;
-        valid[i] = ok ? 0xf : 0;
-        const uint32_t off = ok ? (uint32_t)((x * ldw + r) * 4) : kOOB;
-        w[i] = bload4(rw, off);
-        g[i] = bload4(rg, off);
-        m[i] = bload4(rm, off);
-        v[i] = bload4(rv, off);
-      } else {
-        float ew[4], eg[4], em[4], ev[4];
-        valid[i] = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const bool ok = live && r + k < nr;
-          valid[i] |= ok ? (1 << k) : 0;
-          const uint32_t off = ok ? (uint32_t)((x * ldw + r + k) * 4) : kOOB;
-          ew[k] = bload1(rw, off);
-          eg[k] = bload1(rg, off);
-          em[k] = bload1(rm, off);
-          ev[k] = bload1(rv, off);
-        }
-        w[i] = make_float4(ew[0], ew[1], ew[2], ew[3]);
-        g[i] = make_float4(eg[0], eg[1], eg[2], eg[3]);
-        m[i] = make_float4(em[0], em[1], em[2], em[3]);
-        v[i] = make_float4(ev[0], ev[1], ev[2], ev[3]);
-      }
-    }
-  }
-
-  // owner: this workgroup writes the updated values (to ea.Wout when set, else
-  // in place); every workgroup feeds them to its MFMAs.
-  __device__ __forceinline__ void apply(const EpiArgs& ea, int64_t ldw, float* lds, int tid,
-                                        bool owner) {
-    constexpr int LD = BX + 4;
-    const bool adam = ea.opt.kind != OF_OPT_SGD;
-    const of_param& out = ea.Wout.w ? ea.Wout : ea.W;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = tid + i * 256;
-      if (idx >= NV) continue;
-      const int x = idx / (BR / 4), r = (idx % (BR / 4)) * 4;
-      const int64_t o = base + (int64_t)x * ldw + r;
-      float* pw = reinterpret_cast<float*>(&w[i]);
-      float* pg = reinterpret_cast<float*>(&g[i]);
-      float* pm = reinterpret_cast<float*>(&m[i]);
-      float* pv = reinterpret_cast<float*>(&v[i]);
-      if (valid[i] == 0xf && ((uintptr_t)(out.w + o) & 15u) == 0) {
-        for (int e = 0; e < 4; ++e) opt_update(ea.opt, pw[e], pg[e], pm[e], pv[e]);
-        if (owner) {
-          st4(out.w + o, w[i]);
-          if (out.m) st4(out.m + o, m[i]);
-          if (adam) st4(out.v + o, v[i]);
-          if (out.w_bf16) st_bf16x4(out.w_bf16 + o, w[i]);
-        }
-      } else if (valid[i]) {
-        for (int e = 0; e < 4; ++e) {
-          if (valid[i] & (1 << e)) {
-            opt_update(ea.opt, pw[e], pg[e], pm[e], pv[e]);
-            if (owner) {
-              out.w[o + e] = pw[e];
-              if (out.m) out.m[o + e] = pm[e];
-              if (adam) out.v[o + e] = pv[e];
-              if (out.w_bf16) out.w_bf16[o + e] = f32_to_bf16(pw[e]);
-            }
-          }
-        }
-      }
-      lds[(r + 0) * LD + x] = w[i].x;
-      lds[(r + 1) * LD + x] = w[i].y;
-      lds[(r + 2) * LD + x] = w[i].z;
-      lds[(r + 3) * LD + x] = w[i].w;
-    }
-  }
-};
 
 // -------------------------------------------------------------------- kernel
 // VECS: bit 0 -- 128-bit loads of A allowed, bit 1 -- of B.
@@ -570,7 +348,10 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmProblem pr, EpiArgs ea, i
       float* buf = smem + (c & 1) * STAGE;
       la[s].store(buf, tid);
       if constexpr (EPI == EPI_FWD_FF) {
-        if (c < nch) lf[s].apply(ea, ldw, buf + BOFF, tid, ff_owner);
+        if (c < nch) {
+          lf[s].update(ea, ldw, tid, ff_owner);
+          lf[s].store(buf + BOFF, tid);
+        }
       } else {
         lb[s].store(buf + BOFF, tid);
       }
@@ -885,6 +666,56 @@ static GemmCfg make_cfg(int t, int P, int Q, int R, int64_t target_ctas, int max
 
 static int ff_tile(int P) { return P <= 32 ? TI_32x32 : TI_64x32; }
 
+// The tile and split of least cost among the tiles that run on the bf16 matrix
+// cores, in us: a workgroup alone multiplies at `rate` TFLOP/s, `conc` workgroups
+// share a CU without slowing each other, and a split adds a second pass (a
+// fixed cost plus writing and reading the partials).  Over the chip that is
+// 175 TFLOP/s for 128x128, 160 for 64x128, and for 64x64 90 with one workgroup
+// per CU and 138 with two (measured at 1024 x 2048 x 2048 and up).
+// A weight gradient has no 64x128 tile (its transposing reads of both operands
+// leave no registers for it), and unsplit it takes 64x64: backward-fusion's
+// update of a 128x128 tile leaves a CU's one workgroup waiting for W, m and v
+// (fused / plain, 64 x 8192 x 8192: 364 / 100 us on 128x128, 322 / 115 on 64x64;
+// 1024 x 2048 x 2048: 75 / 51, 67 / 60).
+static GemmCfg cheapest_split(int kind, int P, int Q, int R) {
+  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
+  struct { int t; double rate, conc; } const tiles[3] = {
+      {TI_S128x128, 0.69, 1.0}, {TI_S64x128, kind == EPI_DGRAD ? 0.50 : 0.63, 1.0},
+      {TI_S64x64, 0.38, 1.5}};
+  double best = 1e30;
+  GemmCfg pick{TI_S64x64, 1, (R + 31) / 32 * 32};
+  for (const auto& c : tiles) {
+    if (wg && c.t == TI_S64x128) continue;
+    const int BR = kTileBR[c.t];
+    for (int S = 1; S <= 64; S *= 2) {
+      if (S > 1 && R / S < 4 * BR) continue;
+      const int r_split = ((R + S - 1) / S + BR - 1) / BR * BR;
+      const int Se = (R + r_split - 1) / r_split;
+      if (wg && Se == 1 && c.t == TI_S128x128) continue;
+      const double W = (double)ntiles(c.t, P, Q) * Se;
+      double T = 2e-6 * kTileBP[c.t] * kTileBQ[c.t] * r_split / c.rate *
+                 std::max(1.0, W / (256.0 * c.conc));
+      if (Se > 1) T += 5.0 + (double)P * Q * Se * 8 / 5e6;
+      if (T < best) {
+        best = T;
+        pick = GemmCfg{c.t, Se, r_split};
+      }
+    }
+  }
+  return pick;
+}
+
+// Whether a linear layer's contraction has enough work for those tiles to beat
+// the fp32 ones.  Measured on MI355X, fp32 / bf16 matrix cores: 256 x 1024 x 1024
+// forward 10.6 / 13.5 us, weight gradient 10.2 / 9.2 (fused 13.6 / 13.7, and 2% of an
+// 8-layer step lost); 512 x 1024 x 1024 forward 18.9 / 18.0, data gradient 16.0 / 18.0,
+// weight gradient 14.9 / 13.5 (fused 20.7 / 18.3); 1000 x 1024 x 1024 30.1 / 25.9, 27.4 /
+// 22.2, 25.1 / 23.0; 1024 x 2048 x 2048 86 / 58, 86 / 60, fused 98 / 67.
+static bool split_pays(int kind, int P, int Q, int R) {
+  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
+  return P > 32 && Q > 32 && R >= 64 && 2.0 * P * Q * R >= (wg ? 8e8 : 1.2e9);
+}
+
 static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
   // The forward and the fused forward of at most 64 rows share one tiling (the
   // same tile, splits and split length), so their results are bit-identical;
@@ -893,22 +724,19 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
   // rows, so the update can be written in place.  A fused forward of more
   // rows writes its update to a second buffer set (every row tile computes it,
   // row tile 0 stores it) and takes the plain forward's tiling.
-  if (kind == EPI_FWD_FF)
-    return P <= 64 ? make_cfg(ff_tile(P), P, Q, R, 1024, 8) : select_cfg_default(EPI_FWD, P, Q, R);
+  if (kind == EPI_FWD_FF) return select_cfg_default(EPI_FWD, P, Q, R);
   if (kind == EPI_FWD && P <= 64) {
     GemmCfg c = make_cfg(ff_tile(P), P, Q, R, 1024, 8);
     // Between 33 and 64 rows, with enough columns to fill the chip: 64x128
-    // tiles with the same splits, whose sums equal the 64x32 tile's bit for
-    // bit; a third of the operand loads per flop (measured on MI355X at
-    // 64 x 8192 x 8192: 108 against 115 us).
-    if (P > 32 && ntiles(TI_64x128, P, Q) * c.S >= 256) c.tile = TI_64x128;
+    // tiles on the bf16 matrix cores with the same splits (measured on MI355X at
+    // 64 x 8192 x 8192: 62 us, 82 us on fp32 tiles of that size); the fused
+    // forward of that shape takes 64x32 tiles of the same reduction layout.
+    if (P > 32 && ntiles(TI_S64x128, P, Q) * c.S >= 256) c.tile = TI_S64x128;
     return c;
   }
   if (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) {
-    // A short reduction onto a huge output (an 8192 x 8192 layer at 64 rows):
-    // whole reductions on 64x64 tiles (measured on MI355X: plain 115 us, fused with
-    // Adam 356 us; 127 / 366 us on 128x128 tiles).
-    if (R <= 128 && ntiles(TI_128x128, P, Q) >= 1024) return make_cfg(TI_64x64, P, Q, R, 1, 1);
+    // (A very long reduction onto few outputs stays on the narrow fp32 tiles below.)
+    if (R < 65536 && split_pays(kind, P, Q, R)) return cheapest_split(kind, P, Q, R);
     if (R <= 1024 && ntiles(TI_32x32, P, Q) >= 512) return make_cfg(TI_32x32, P, Q, R, 1, 1);
     // A very long reduction onto few outputs (the pixel rows of a 1x1
     // convolution, 65k-400k rows onto a few hundred weights): up to 256
@@ -932,6 +760,7 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
       return make_cfg(P >= 65536 ? TI_256x32 : (Q <= 32 ? TI_32x32 : TI_64x64), P, Q, R, 1, 1);
     return make_cfg(Q <= 32 ? TI_64x32 : TI_64x64, P, Q, R, 1, 1);
   }
+  if (split_pays(kind, P, Q, R)) return cheapest_split(kind, P, Q, R);
   if (P <= 64 && ntiles(TI_64x64, P, Q) >= 64) return make_cfg(TI_64x64, P, Q, R, 1024, 8);
   // Larger outputs: the biggest tile that still gives one workgroup per CU; no
   // reduction split (each split costs a second kernel, ~4 us back to back).
@@ -963,7 +792,7 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
 // second pass (fixed cost plus reading and writing the partials).  The rule
 // depends on (P, Q, R) only, so the eager and backward-fusion weight gradients
 // still share their tiling.
-static GemmCfg select_cfg_conv(int P, int Q, int R) {
+static GemmCfg select_cfg_conv(int kind, int P, int Q, int R) {
   // A first layer of at most 32 filters over few input channels (a 3-channel
   // image stem: 3x3x3 = 27 reduction elements) at 65k pixels or more: its
   // forward takes 256x32 tiles, its weight gradient 32x32 tiles split over the
@@ -971,6 +800,10 @@ static GemmCfg select_cfg_conv(int P, int Q, int R) {
   // weight gradient 99 -> 62 us).
   if (R <= 32 && Q <= 32 && P >= 65536) return make_cfg(TI_256x32, P, Q, R, 1, 1);
   if (Q <= 32 && P <= 32 && R >= 65536) return make_cfg(TI_32x32, P, Q, R, 256, 256);
+  // Enough work for the tiles on the bf16 matrix cores (measured on MI355X, fp32 /
+  // bf16 matrix cores, forward, data and weight gradient: 128 x 8 x 8 x 256 -> 256
+  // 100 / 62, 106 / 69, 106 / 80 us; 16 x 14 x 14 x 96 -> 160 23 / 19, 25 / 20, 23 / 19).
+  if (P > 32 && Q > 32 && R >= 64 && 2.0 * P * Q * R >= 5e8) return cheapest_split(kind, P, Q, R);
   static const double kEff[6] = {0.489, 0.283, 0.617, 0.488, 0.714, 0.765};
   static const int kConc[6] = {1, 4, 3, 4, 2, 1};
   static const int kSplits[8] = {1, 2, 4, 8, 16, 32, 64, 128};
@@ -997,7 +830,7 @@ static GemmCfg select_cfg_conv(int P, int Q, int R) {
 }
 
 static GemmCfg select_cfg_any(int kind, int P, int Q, int R, int conv) {
-  return conv ? select_cfg_conv(P, Q, R) : select_cfg_default(kind, P, Q, R);
+  return conv ? select_cfg_conv(kind, P, Q, R) : select_cfg_default(kind, P, Q, R);
 }
 
 #ifdef OPFUSE_TUNING
@@ -1077,21 +910,6 @@ static hipError_t launch_kind(const GemmCfg& c, const GemmProblem& pr, const Epi
       if constexpr (EPI == EPI_FWD_FF) return hipErrorInvalidValue;
       else return launch_t<T128x128, EPI>(c, pr, ea, ws, vec_ops, vec_epi, s);
     case TI_256x32: return launch_t<T256x32, EPI>(c, pr, ea, ws, vec_ops, vec_epi, s);
-    case TI_64x128:
-      // the plain forward of linear layers only (its fused counterpart keeps
-      // T64x32, whose sums it reproduces)
-      if constexpr (EPI == EPI_FWD) {
-        if (pr.conv) return hipErrorInvalidValue;
-        dim3 grid((pr.P + 63) / 64, (pr.Q + 127) / 128, c.S + c.cz);
-        if (vec_ops == 3)
-          hipLaunchKernelGGL((gemm_kernel<T64x128, EPI, 3, false>), grid, dim3(256), 0, s, pr, ea,
-                             c.r_split, (float*)ws, vec_epi);
-        else
-          hipLaunchKernelGGL((gemm_kernel<T64x128, EPI, 0, false>), grid, dim3(256), 0, s, pr, ea,
-                             c.r_split, (float*)ws, vec_epi);
-        return hipGetLastError();
-      }
-      return hipErrorInvalidValue;
     case TI_32x32D:
     case TI_32x32D8:
       // direct loads exist for the linear forward and data gradient; the same
@@ -1175,6 +993,10 @@ hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, vo
   // forward given it takes 128x64 with the same splits (the same reduction
   // ranges and workspace).
   if (kind == EPI_FWD_FF && c.tile == TI_128x128) c.tile = TI_128x64;
+  // The fused forward's registers hold W, g, m and v, so it takes smaller tiles
+  // with the same splits and, per output element, the same MFMA sequence.
+  if (kind == EPI_FWD_FF && c.tile == TI_S128x128) c.tile = TI_S64x64;
+  if (kind == EPI_FWD_FF && c.tile == TI_S64x128) c.tile = TI_S64x32;
   EpiArgs ea = ea_in;
   ea.carry.cz = 0;
   if (ea.carry.t[0].p.w) {
@@ -1187,7 +1009,11 @@ hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, vo
   const bool wg = (kind == EPI_WGRAD || kind == EPI_WGRAD_BF);
   const int with_db = wg && ea.with_db;
   hipError_t e;
-  switch (kind) {
+  if (c.tile >= TI_S128x128)
+    e = (pr.conv ? split_launch_conv : split_launch_linear)(kind, c.tile - TI_S128x128, c.S, c.cz,
+                                                            c.r_split, pr, ea, ws, vec_ops, vec_epi,
+                                                            stream);
+  else switch (kind) {
     case EPI_FWD: e = launch_kind<EPI_FWD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
     case EPI_FWD_FF: e = launch_kind<EPI_FWD_FF>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
     case EPI_DGRAD: e = launch_kind<EPI_DGRAD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
