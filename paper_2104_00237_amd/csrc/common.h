@@ -127,21 +127,48 @@ __device__ __forceinline__ float bf16_round(float f) {
   return __uint_as_float(((uint32_t)f32_to_bf16(f)) << 16);
 }
 
+// Standard normal distribution function, Phi(z).  For t = |z|, Phi(-t) = 2^q(t) with
+// q a polynomial fitted to log2 Phi(-t) in float64 (iteratively reweighted least
+// squares for the least largest error, q(0) = -1, t to 14; the leading coefficient
+// is negative, so it falls without bound beyond).  Absolute error at most 3.6e-8,
+// rms 0.8e-8, where 0.5 * (1 + erff(z / sqrt 2)) has 5.7e-8 and 1.7e-8 and rounds to
+// 0 below -5.6; a third of its instructions, which an epilogue of a large product
+// pays for (16.7M elements: about 25 us less).
+__device__ __forceinline__ float normal_cdf(float z) {
+  const float t = fabsf(z);
+  float q = -4.58950412e-11f;
+  q = __fmaf_rn(q, t, 3.09264059e-09f);
+  q = __fmaf_rn(q, t, -8.89342644e-08f);
+  q = __fmaf_rn(q, t, 1.42966883e-06f);
+  q = __fmaf_rn(q, t, -1.4111617e-05f);
+  q = __fmaf_rn(q, t, 8.71800221e-05f);
+  q = __fmaf_rn(q, t, -0.000302401982f);
+  q = __fmaf_rn(q, t, 2.86804916e-05f);
+  q = __fmaf_rn(q, t, 0.00692749722f);
+  q = __fmaf_rn(q, t, -0.0524358787f);
+  q = __fmaf_rn(q, t, -0.459220737f);
+  q = __fmaf_rn(q, t, -1.15110433f);
+  q = __fmaf_rn(q, t, -1.f);
+  const float h = __builtin_amdgcn_exp2f(q);
+  return z < 0.f ? h : __fsub_rn(1.f, h);
+}
+
 // Derivative of the forward activation, evaluated from the saved tensor the
 // dgrad epilogue receives: Y for ReLU (Y > 0 exactly when Z > 0), Z for GELU.
 __device__ __forceinline__ float act_grad(int act, float saved) {
   if (act == OF_ACT_RELU) return saved > 0.f ? 1.f : 0.f;
   if (act == OF_ACT_GELU) {
-    const float cdf = 0.5f * (1.f + erff(saved * 0.70710678118654752f));
-    const float pdf = 0.39894228040143268f * expf(-0.5f * saved * saved);
-    return cdf + saved * pdf;
+    // pdf(z) = 2^(-z^2 / (2 ln 2)) / sqrt(2 pi)
+    const float pdf = 0.39894228040143268f *
+                      __builtin_amdgcn_exp2f(__fmul_rn(-0.72134752044448170f, __fmul_rn(saved, saved)));
+    return __fmaf_rn(saved, pdf, normal_cdf(saved));
   }
   return 1.f;
 }
 
 __device__ __forceinline__ float act_fwd(int act, float z) {
   if (act == OF_ACT_RELU) return z > 0.f ? z : 0.f;
-  if (act == OF_ACT_GELU) return z * (0.5f * (1.f + erff(z * 0.70710678118654752f)));
+  if (act == OF_ACT_GELU) return __fmul_rn(z, normal_cdf(z));
   return z;
 }
 
@@ -315,6 +342,8 @@ hipError_t split_launch_conv(int kind, int tile, int S, int cz, int r_split, con
                              hipStream_t stream);
 // bf16-operand contractions (operands rounded to bf16, fp32 accumulation);
 // kinds EPI_FWD, EPI_DGRAD, EPI_WGRAD, EPI_WGRAD_BF; strided operands only.
+hipError_t gemm_bf16_wide_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, int cz,
+                                 hipStream_t stream);
 size_t gemm_bf16_workspace_bytes(int kind, int P, int Q, int R);
 hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, void* ws,
                             hipStream_t stream);

@@ -620,6 +620,19 @@ static int bvec_flags(const GemmProblem& pr, int kind, const EpiArgs& ea, int* v
   return (va ? 1 : 0) | (vb ? 2 : 0);
 }
 
+// Whether the 256x256-tile kernel takes a forward or a data gradient: 16-byte
+// pieces of both operands whole or absent, offsets within a buffer descriptor,
+// and at least 160 tiles of them.
+static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_ops) {
+  if ((kind != EPI_FWD && kind != EPI_DGRAD) || vec_ops != 3 || !pr.b_bf16) return false;
+  for (int64_t ld : {pr.a_sp, pr.b_sq, pr.b_sr, ea.ldo, ea.ldz, ea.ldp, ea.ldr})
+    if (ld > (1 << 20)) return false;   // 32-bit offsets within a tile
+  if (kind == EPI_DGRAD && (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0 ||
+                            (int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31)))
+    return false;
+  return (int64_t)((pr.P + 255) / 256) * ((pr.Q + 255) / 256) >= 160;
+}
+
 hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& ea_in, void* ws,
                             hipStream_t stream) {
   GemmProblem pr = pr_in;
@@ -641,6 +654,15 @@ hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& e
   const int vec_ops = bvec_flags(pr, kind, ea, &vec_epi);
   const int with_db = (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) && ea.with_db;
   hipError_t e;
+#ifdef OPFUSE_TUNING
+  if (!getenv("OPFUSE_NOWIDE"))
+#endif
+  if (wide_ok(kind, pr, ea, vec_ops)) {
+    const int64_t tiles = (int64_t)((pr.P + 255) / 256) * ((pr.Q + 255) / 256);
+    const int cz = ea.carry.t[0].p.w ? carry_slices(ea.carry, tiles) : 0;
+    ea.carry.cz = cz;
+    return gemm_bf16_wide_launch(kind, pr, ea, cz, stream);
+  }
   switch (kind) {
     case EPI_FWD: e = blaunch_kind<EPI_FWD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
     case EPI_DGRAD: e = blaunch_kind<EPI_DGRAD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;

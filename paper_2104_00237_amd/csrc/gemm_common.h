@@ -21,13 +21,16 @@ constexpr uint32_t kOOB = 0x80000000u;  // beyond num_records: reads as 0
 // live in scalar registers.  Reading it from the first lane says so to the
 // compiler, which otherwise may not prove it and wraps every load in a loop
 // over the distinct values.
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base) {
+// bytes: how far from `base` accesses reach (2^31-1 unless the end matters).
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, int bytes = 0x7fffffff) {
   const uint64_t a = (uint64_t)base;
+  // (unsigned variables: readfirstlane returns a signed int, which would extend
+  // into the upper half)
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
   void* ub = (void*)(((uint64_t)hi << 32) | lo);
-  // raw buffer, stride 0, 2^31-1 bytes addressable from `base`
-  return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, 0x7fffffff, 0x00020000);
+  // raw buffer, stride 0
+  return __builtin_amdgcn_make_buffer_rsrc(ub, (short)0, bytes, 0x00020000);
 }
 // Descriptor of `base + off` elements, or of nothing when `base` is NULL (an
 // optional state tensor): every load through it reads 0 and every store is
