@@ -350,14 +350,14 @@ __device__ __forceinline__ void split_reduce_body(int P, int Q, int S, EpiArgs& 
   }
 }
 
-// Long split lists: G = 8 consecutive lanes (one wave holds whole groups)
+// Long split lists: G consecutive lanes (8 or 32; one wave holds whole groups)
 // share each float4 item of the output.  Lane j sums the splits
-// j*SG .. (j+1)*SG - 1 in split order (SG = ceil(S / 8)); the group's first
-// lane then adds the 8 sums in lane order and runs the epilogue.  A single
+// j*SG .. (j+1)*SG - 1 in split order (SG = ceil(S / G)); the group's first
+// lane then adds the G sums in lane order and runs the epilogue.  A single
 // thread per item would wait for S / 8 load latencies in a row.  The order
 // is fixed, so every ordering that shares a tiling still gets the same bits.
 // The bias-gradient partials are summed the same way.
-template <int EPI>
+template <int EPI, int G = 8>
 __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiArgs& ea,
                                                        const float* __restrict__ partial,
                                                        int vec_epi, int with_db) {
@@ -365,10 +365,10 @@ __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiA
   const int nq4 = (Q + 3) / 4;
   const int64_t total = (int64_t)P * nq4;
   const int64_t PQ = (int64_t)P * Q;
-  const int lane = threadIdx.x & 63, j = lane & 7, lead = lane & ~7;
-  const int SG = (S + 7) / 8;
+  const int lane = threadIdx.x & 63, j = lane & (G - 1), lead = lane & ~(G - 1);
+  const int SG = (S + G - 1) / G;
   const int kb = min(S, j * SG), ke = min(S, kb + SG);
-  const int64_t groups = (int64_t)gridDim.x * 32;
+  const int64_t groups = (int64_t)gridDim.x * (256 / G);
   // lanes [0, 4): this lane's partial sums of the item's (up to) 4 elements
   auto lane_sum = [&](const float* src, int n, bool v4, float (&acc)[4]) {
     for (int e = 0; e < 4; ++e) acc[e] = 0.f;
@@ -394,7 +394,7 @@ __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiA
       }
     }
   };
-  for (int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3; idx < total; idx += groups) {
+  for (int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G; idx < total; idx += groups) {
     const int p = (int)(idx / nq4), q = (int)(idx % nq4) * 4;
     const int n = min(4, Q - q);
     const int64_t oo = (int64_t)p * ea.ldo + q;
@@ -408,7 +408,7 @@ __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiA
     for (int e = 0; e < 4; ++e) {
       c[e] = __shfl(acc[e], lead);
 #pragma unroll
-      for (int g = 1; g < 8; ++g) c[e] = __fadd_rn(c[e], __shfl(acc[e], lead + g));
+      for (int g = 1; g < G; ++g) c[e] = __fadd_rn(c[e], __shfl(acc[e], lead + g));
     }
     if (pre) {
       bf_apply(ea, bp, c, oo);
@@ -420,7 +420,7 @@ __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiA
   }
   if (with_db) {
     const float* dbp = partial + (int64_t)S * PQ;
-    for (int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3; p < P; p += groups) {
+    for (int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) / G; p < P; p += groups) {
       float acc = 0.f;
       for (int k0 = kb; k0 < ke; k0 += 8) {
         float t[8];
@@ -432,7 +432,7 @@ __device__ __forceinline__ void split_reduce_coop_body(int P, int Q, int S, EpiA
       }
       float s = __shfl(acc, lead);
 #pragma unroll
-      for (int g = 1; g < 8; ++g) s = __fadd_rn(s, __shfl(acc, lead + g));
+      for (int g = 1; g < G; ++g) s = __fadd_rn(s, __shfl(acc, lead + g));
       if (j == 0) bias_epilogue<EPI>(ea, (int)p, s);
     }
   }

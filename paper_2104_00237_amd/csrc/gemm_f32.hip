@@ -619,11 +619,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_direct_kernel(GemmProblem pr, Ep
 
 // Sum the split partials (8 lanes per output item for long split lists),
 // then run the epilogue.
-template <int EPI>
+template <int EPI, int G>
 __global__ __launch_bounds__(256) void split_reduce_coop_kernel(int P, int Q, int S, EpiArgs ea,
                                                                 const float* __restrict__ partial,
                                                                 int vec_epi, int with_db) {
-  split_reduce_coop_body<EPI>(P, Q, S, ea, partial, vec_epi, with_db);
+  split_reduce_coop_body<EPI, G>(P, Q, S, ea, partial, vec_epi, with_db);
 }
 
 // Sum the split partials in split order, then run the epilogue.
@@ -927,16 +927,24 @@ static hipError_t launch_kind(const GemmCfg& c, const GemmProblem& pr, const Epi
 
 // Split counts from which 8 lanes share each output item of the reduction pass.
 constexpr int kCoopSplits = 16;
+// ... and beyond which 32 do: a lane then waits for one group of 8 loads instead of
+// several in turn (242 splits of 144 x 24: 14.4 us with 8 lanes).
+constexpr int kWideSplits = 64;
 
 template <int EPI>
 static hipError_t launch_reduce(const GemmCfg& c, const GemmProblem& pr, const EpiArgs& ea,
                                 void* ws, int vec_epi, int with_db, hipStream_t s) {
   const int64_t work = (int64_t)pr.P * ((pr.Q + 3) / 4);
   if (c.S >= kCoopSplits) {
-    const int64_t lanes = std::max<int64_t>(work, with_db ? pr.P : 0) * 8;
+    const int G = c.S > kWideSplits ? 32 : 8;
+    const int64_t lanes = std::max<int64_t>(work, with_db ? pr.P : 0) * G;
     const int blocks = (int)std::min<int64_t>(2048, std::max<int64_t>(1, (lanes + 255) / 256));
-    hipLaunchKernelGGL((split_reduce_coop_kernel<EPI>), dim3(blocks), dim3(256), 0, s, pr.P, pr.Q,
-                       c.S, ea, (const float*)ws, vec_epi, with_db);
+    if (G == 32)
+      hipLaunchKernelGGL((split_reduce_coop_kernel<EPI, 32>), dim3(blocks), dim3(256), 0, s, pr.P,
+                         pr.Q, c.S, ea, (const float*)ws, vec_epi, with_db);
+    else
+      hipLaunchKernelGGL((split_reduce_coop_kernel<EPI, 8>), dim3(blocks), dim3(256), 0, s, pr.P,
+                         pr.Q, c.S, ea, (const float*)ws, vec_epi, with_db);
     return hipGetLastError();
   }
   const int blocks = (int)std::min<int64_t>(2048, std::max<int64_t>(1, (work + 255) / 256));
@@ -988,6 +996,7 @@ static int vec_flags(const GemmProblem& pr, int kind, const EpiArgs& ea, int* ve
 
 hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, void* ws,
                        hipStream_t stream) {
+  if (gemm_rows_ok(kind, pr, ea_in)) return gemm_rows_launch(kind, pr, ea_in, stream);
   GemmCfg c = select_cfg(kind, pr.P, pr.Q, pr.R, pr.conv);
   // The 128x128 tile leaves no LDS for forward-fusion's bias row; a fused
   // forward given it takes 128x64 with the same splits (the same reduction
