@@ -232,6 +232,14 @@ __device__ __forceinline__ float update1(const OptK& o, const of_param& P, float
   return opt_apply1(o, P, opt_load1(o, P, off), g, off);
 }
 
+// Workgroups go to the 8 XCDs (each with its own L2) round-robin.  Renumbers
+// workgroup b of n so that each XCD gets one contiguous run of them: neighbours
+// that read the same data then share an L2.  Every number is still taken once.
+__device__ __forceinline__ int xcd_run(int b, int n) {
+  const int per = n >> 3;
+  return b < per * 8 ? (b & 7) * per + (b >> 3) : b;
+}
+
 inline bool aligned16(const void* p) { return (((uintptr_t)p) & 15u) == 0; }
 
 // ---------------------------------------------------------------- GEMM API

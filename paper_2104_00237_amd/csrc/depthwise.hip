@@ -6,7 +6,9 @@
 // forward, the stride-1 data gradient and the filter gradient walk columns of
 // a few rows with the 3x3 window in registers, so a row step loads only the
 // new window rows; the stride-2 data gradient (at most four taps per input
-// pixel) takes one pixel per thread.
+// pixel) takes one pixel per thread.  Neighbouring columns share two thirds of what
+// they read, so every kernel's workgroups are renumbered to keep neighbours on
+// one XCD (xcd_run): round-robin, three XCDs fetched each column.
 //
 // Filter gradient: dW[ky,kx,c] = sum over (n,h,w) of dy[n,h,w,c] *
 // x[n,h+ky-1,w+kx-1,c], db[c] = sum of dy[n,h,w,c].  Pass 1 splits the output
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(256) void dw_dgrad_kernel(const float* __restrict__
                                                        const float* __restrict__ prev,
                                                        int act_prev, float* __restrict__ dx,
                                                        DwShape s, int total) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = xcd_run(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= total) return;
   const int c = i % s.C, p = i / s.C;
   const int col = p % s.W, t = p / s.W, row = t % s.H, n = t / s.H;
@@ -186,9 +188,11 @@ __global__ __launch_bounds__(256) void dw_wgrad_partial_kernel(const float* __re
                                                                int nseg) {
   extern __shared__ float red[];   // [16][DW_TAPS][cb]
   const int cl = threadIdx.x % cb, sub = threadIdx.x / cb;
-  const int c = blockIdx.x * cb + cl;
   const int U = s.N * s.Wo * nseg;  // units
-  const int u0 = blockIdx.y * per_slice, u1 = min(U, u0 + per_slice);
+  const int slice = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const int bx = slice % gridDim.x, by = slice / gridDim.x;   // channel block, slice
+  const int c = bx * cb + cl;
+  const int u0 = by * per_slice, u1 = min(U, u0 + per_slice);
   float acc[4][DW_TAPS];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
@@ -205,7 +209,7 @@ __global__ __launch_bounds__(256) void dw_wgrad_partial_kernel(const float* __re
 #pragma unroll
     for (int k = 0; k < DW_TAPS; ++k) red[((sub + 4 * j) * DW_TAPS + k) * cb + cl] = acc[j][k];
   __syncthreads();
-  dw_slice_sums(red, cb, blockIdx.x * cb, s.C, part + (int64_t)blockIdx.y * DW_TAPS * s.C);
+  dw_slice_sums(red, cb, bx * cb, s.C, part + (int64_t)by * DW_TAPS * s.C);
 }
 
 // ---- four-channel variants (C % 4 == 0, 16-byte aligned tensors): one thread
@@ -222,7 +226,7 @@ __global__ __launch_bounds__(256) void dw_dgrad4_kernel(const float* __restrict_
                                                         const float* __restrict__ prev,
                                                         int act_prev, float* __restrict__ dx,
                                                         DwShape s, int quads) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = xcd_run(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= quads) return;
   const int Cq = s.C >> 2;
   const int c = (i % Cq) * 4, p = i / Cq;
@@ -262,9 +266,11 @@ __global__ __launch_bounds__(256) void dw_wgrad_partial4_kernel(const float* __r
   extern __shared__ float red[];   // [16][DW_TAPS][cb]
   const int nq = cb / 4;
   const int q = threadIdx.x % nq, sub = threadIdx.x / nq;
-  const int c = blockIdx.x * cb + q * 4;
   const int U = s.N * s.Wo * nseg;  // units
-  const int u0 = blockIdx.y * per_slice, u1 = min(U, u0 + per_slice);
+  const int slice = xcd_run(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const int bx = slice % gridDim.x, by = slice / gridDim.x;   // channel block, slice
+  const int c = bx * cb + q * 4;
+  const int u0 = by * per_slice, u1 = min(U, u0 + per_slice);
   float4 acc[DW_TAPS];
 #pragma unroll
   for (int k = 0; k < DW_TAPS; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -280,7 +286,7 @@ __global__ __launch_bounds__(256) void dw_wgrad_partial4_kernel(const float* __r
     r[3] = acc[k].w;
   }
   __syncthreads();
-  dw_slice_sums(red, cb, blockIdx.x * cb, s.C, part + (int64_t)blockIdx.y * DW_TAPS * s.C);
+  dw_slice_sums(red, cb, bx * cb, s.C, part + (int64_t)by * DW_TAPS * s.C);
 }
 
 // ---- column sweeps for the forward (strides 1 and 2) and the stride-1 data
@@ -304,8 +310,11 @@ __device__ __forceinline__ float4 dwv_dact(float4 acc, int act, const float* p, 
   return make_float4(__fmul_rn(acc.x, act_grad(act, v.x)), __fmul_rn(acc.y, act_grad(act, v.y)),
                      __fmul_rn(acc.z, act_grad(act, v.z)), __fmul_rn(acc.w, act_grad(act, v.w)));
 }
-__device__ __forceinline__ void dwv_store(float* p, float v) { *p = v; }
-__device__ __forceinline__ void dwv_store(float* p, float4 v) { st4(p, v); }
+__device__ __forceinline__ void dwv_store(float* p, float v) { __builtin_nontemporal_store(v, p); }
+__device__ __forceinline__ void dwv_store(float* p, float4 v) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(f4{v.x, v.y, v.z, v.w}, reinterpret_cast<f4*>(p));
+}
 
 template <int S, class V>
 __global__ __launch_bounds__(256) void dw_fwd_sweep_kernel(const float* __restrict__ x,
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(256) void dw_fwd_sweep_kernel(const float* __restri
                                                            float* __restrict__ y, DwShape s,
                                                            int act, int seg_rows, int nseg, int nq,
                                                            int total) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = xcd_run(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= total) return;
   constexpr int VW = sizeof(V) / sizeof(float);
   const int c = (i % nq) * VW, u = i / nq;
@@ -401,7 +410,7 @@ __global__ __launch_bounds__(256) void dw_dgrad_sweep_kernel(const float* __rest
                                                              int act_prev, float* __restrict__ dx,
                                                              DwShape s, int seg_rows, int nseg,
                                                              int nq, int total) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  const int i = xcd_run(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (i >= total) return;
   constexpr int VW = sizeof(V) / sizeof(float);
   const int c = (i % nq) * VW, u = i / nq;

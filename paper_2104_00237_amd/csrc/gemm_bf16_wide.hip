@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
         if (ea.bias) c[k] = __fadd_rn(c[k], bias[j]);
         if (ea.z)
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c[k]), rz,
-                                                loc(ea.ldz, j, 4) + row(ea.ldz, i, k, 4), 0, 0);
+                                                loc(ea.ldz, j, 4) + row(ea.ldz, i, k, 4), 0, 2);
       }
     }
     if constexpr (EPI == EPI_FWD) {
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
 #pragma unroll
       for (int k = 0; k < 16; ++k)
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(c[k]), ro,
-                                              loc(ea.ldo, j, 4) + row(ea.ldo, i, k, 4), 0, 0);
+                                              loc(ea.ldo, j, 4) + row(ea.ldo, i, k, 4), 0, 2);
     }
   };
   each(std::make_integer_sequence<int, 16>{}, block);

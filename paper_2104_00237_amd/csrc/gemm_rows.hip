@@ -89,13 +89,13 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(GemmProblem pr, EpiArgs 
         float v = acc[k];
         if constexpr (EPI == EPI_FWD) {
           if (ea.bias) v = __fadd_rn(v, bias);
-          if (ea.z) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rz, at(ea.ldz, k, j), 0, 0);
+          if (ea.z) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rz, at(ea.ldz, k, j), 0, 2);
           v = act_fwd(ea.act, v);
         } else if (dact) {
           v = __fmul_rn(v, act_grad(ea.act, sv[k]));
         }
         if (ea.res) v = __fadd_rn(v, rs[k]);
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ro, at(ea.ldo, k, j), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), ro, at(ea.ldo, k, j), 0, 2);
       }
     }
 #pragma unroll
