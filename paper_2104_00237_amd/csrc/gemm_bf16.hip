@@ -482,6 +482,9 @@ static int64_t bntiles(int t, int P, int Q) {
   return (int64_t)((P + kBTileBP[t] - 1) / kBTileBP[t]) * ((Q + kBTileBQ[t] - 1) / kBTileBQ[t]);
 }
 
+constexpr int64_t kWideTiles = 160, kWgradTiles = 192;   // see wide_ok, wgrad_ok
+static int64_t tiles256(int P, int Q) { return (int64_t)((P + 255) / 256) * ((Q + 255) / 256); }
+
 // 128x256 eight-wave tiles for large outputs (at least 512 of them) and, in
 // a forward, for long reductions (at least 128 tiles, 2048 or more reduction
 // elements); else 128x128 tiles when the output has enough of them, else
@@ -507,6 +510,14 @@ static BCfg bselect_default(int kind, int P, int Q, int R) {
   if (kind == EPI_FWD)
     while (S < 8 && (R + S - 1) / S > 2048) S *= 2;
   S = std::min(S, std::min(8, std::max(1, R / (4 * BR))));
+  // Shapes that the kernels with direct loads take unsplit when the operands'
+  // storage and alignment allow: the same order of sums here, so that results do
+  // not depend on either.
+  if (kind == EPI_FWD || kind == EPI_DGRAD) {
+    if (tiles256(P, Q) >= kWideTiles) S = 1;
+  } else if (bntiles(BTI_128x128, P, Q) >= kWgradTiles) {
+    S = 1;
+  }
   int r_split = (((R + S - 1) / S) + BR - 1) / BR * BR;
   S = (R + r_split - 1) / r_split;
   return BCfg{t, S, r_split};
@@ -630,7 +641,20 @@ static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_
   if (kind == EPI_DGRAD && (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0 ||
                             (int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31)))
     return false;
-  return (int64_t)((pr.P + 255) / 256) * ((pr.Q + 255) / 256) >= 160;
+  return tiles256(pr.P, pr.Q) >= kWideTiles;
+}
+
+// Whether the weight-gradient kernel with direct loads takes a weight gradient:
+// X stored as bf16 in whole 16-byte pieces, dZ in whole quads, offsets within a
+// descriptor, and enough tiles to fill the chip unsplit (192 is three quarters of
+// it: a 3072 x 1024 layer).  Outputs of 512 128x256 tiles stay on those.
+static bool wgrad_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_ops) {
+  if ((kind != EPI_WGRAD && kind != EPI_WGRAD_BF) || vec_ops != 3 || !pr.b_bf16) return false;
+  if (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0) return false;
+  if ((int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31) || (int64_t)pr.R * pr.a_sr * 4 >= (1LL << 31) ||
+      ea.ldo > (1 << 22))
+    return false;
+  return bntiles(BTI_128x128, pr.P, pr.Q) >= kWgradTiles && bntiles(BTI_128x256, pr.P, pr.Q) < 512;
 }
 
 hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& ea_in, void* ws,
@@ -654,12 +678,9 @@ hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& e
   const int vec_ops = bvec_flags(pr, kind, ea, &vec_epi);
   const int with_db = (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) && ea.with_db;
   hipError_t e;
-#ifdef OPFUSE_TUNING
-  if (!getenv("OPFUSE_NOWIDE"))
-#endif
+  if (wgrad_ok(kind, pr, ea, vec_ops)) return wgrad_bf16_launch(kind, pr, ea, stream);
   if (wide_ok(kind, pr, ea, vec_ops)) {
-    const int64_t tiles = (int64_t)((pr.P + 255) / 256) * ((pr.Q + 255) / 256);
-    const int cz = ea.carry.t[0].p.w ? carry_slices(ea.carry, tiles) : 0;
+    const int cz = ea.carry.t[0].p.w ? carry_slices(ea.carry, tiles256(pr.P, pr.Q)) : 0;
     ea.carry.cz = cz;
     return gemm_bf16_wide_launch(kind, pr, ea, cz, stream);
   }

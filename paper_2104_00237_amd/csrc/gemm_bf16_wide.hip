@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
   auto request = [&](char* a, char* b, int c) {    // chunk c to LDS (A as fp32: not here)
     const int nr = nr_of(c);   // 0 past the end: zeros
     if constexpr (!A32) da(a, ra, nr, (uint32_t)c * (BR * 2), wave);
-    db(b, rb, nr, B_RC ? (uint32_t)c * (BR * 2) : (uint32_t)(c * BR * ldb * 2), wave);
+    db(b, rb, nr, nr == 0 ? 0u : B_RC ? (uint32_t)c * (BR * 2) : (uint32_t)(c * BR * ldb * 2), wave);
   };
   auto read = [&](Frags& d, const char* a, const char* b, int k) {
 #pragma unroll
@@ -372,6 +372,267 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
     }
   };
   each(std::make_integer_sequence<int, 16>{}, block);
+}
+
+// ------------------------------------------------------------ weight gradient
+// dW[p, q] = sum_r dZ[r, p] X[r, q] on 128x128 tiles, both operands output-
+// contiguous: dZ (fp32) through registers, X (bf16) straight to LDS, both read with
+// ds_read_b64_tr_b16; the main loop is the one above with 64x64 sub-tiles.  The
+// update runs on the accumulators: W, m and v are requested a 32x32 block ahead
+// and moved in 128-byte row segments.  Bound by LDS and the loads (768 clocks of
+// either per chunk, 512 of MFMAs), then by the update's memory traffic.
+// 1024 x 4096 over 4096 rows with AdamW: 111 us on the general kernel.
+namespace {
+
+constexpr int WT = 128;                  // tile rows and columns
+constexpr int WOPB = WT * BR * 2;        // bytes of one operand's chunk in LDS
+
+__device__ __forceinline__ wbf16x8_t wfrag(const char* lds, int x0, int k, int lane) {
+  const int r = k * 16 + (lane >> 5) * 8 + ((lane & 15) >> 2);
+  const int x = x0 + (lane & 16) + (lane & 3) * 4;
+  const char* a = lds + r * 256 + ((x * 2) ^ ((r & 3) << 6));
+  typedef __attribute__((address_space(3))) wshort4_t* lp;
+  const wshort4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)a);
+  const wshort4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(a + 4 * 256));
+  return __builtin_bit_cast(wbf16x8_t, (wshort8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+}  // namespace
+
+template <int EPI>
+__global__ __launch_bounds__(256, 1) void wgrad_bf16_kernel(GemmProblem pr, EpiArgs ea) {
+  static_assert(EPI == EPI_WGRAD || EPI == EPI_WGRAD_BF, "weight gradients");
+  constexpr bool BF = EPI == EPI_WGRAD_BF;
+  __shared__ __attribute__((aligned(1024))) char sa0[WOPB], sa1[WOPB], sb0[WOPB], sb1[WOPB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = wave & 1, wq = wave >> 1;
+  int tx, ty;
+  xcd_tile(tx, ty);
+  const int p0 = tx * WT, q0 = ty * WT;
+  const int np = pr.P - p0, nq = pr.Q - q0;
+  const int nch = (pr.R + BR - 1) / BR;
+  const rsrc_t ra = make_rsrc(pr.A + p0);
+  const rsrc_t rb = make_rsrc((const char*)pr.B + (int64_t)q0 * 2);
+  const int64_t lda = pr.a_sr, ldb = pr.b_sr;
+
+  float4 reg[8];
+  float dbs[4] = {0.f, 0.f, 0.f, 0.f};   // column sums of dZ: a thread's quads share their columns
+  const int ax = (tid & 31) * 4, ar = tid >> 5;
+  auto row_of = [&](int i) { return (i >> 2) * 32 + ar * 4 + (i & 3); };   // quad i's row of the chunk
+  auto nr_of = [&](int c) { return c < nch ? min(BR, pr.R - c * BR) : 0; };
+  auto load = [&](int c) {
+    const int nr = nr_of(c);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = row_of(i);
+      reg[i] = bload4(ra, ax < np && r < nr ? (uint32_t)((((int64_t)c * BR + r) * lda + ax) * 4) : kOOB);
+    }
+  };
+  auto put = [&](char* lds, int i) {   // quad i, rounded to nearest even
+    const int r = row_of(i);
+    *reinterpret_cast<uint2*>(lds + r * 256 + ((ax * 2) ^ ((r & 3) << 6))) =
+        make_uint2(cvt2(reg[i].x, reg[i].y), cvt2(reg[i].z, reg[i].w));
+    if ((i & 3) == 3) {   // four rows at a time: the order of the general kernel's sums
+      const float4 &s0 = reg[i - 3], &s1 = reg[i - 2], &s2 = reg[i - 1], &s3 = reg[i];
+      dbs[0] = __fadd_rn(dbs[0], __fadd_rn(__fadd_rn(__fadd_rn(s0.x, s1.x), s2.x), s3.x));
+      dbs[1] = __fadd_rn(dbs[1], __fadd_rn(__fadd_rn(__fadd_rn(s0.y, s1.y), s2.y), s3.y));
+      dbs[2] = __fadd_rn(dbs[2], __fadd_rn(__fadd_rn(__fadd_rn(s0.z, s1.z), s2.z), s3.z));
+      dbs[3] = __fadd_rn(dbs[3], __fadd_rn(__fadd_rn(__fadd_rn(s0.w, s1.w), s2.w), s3.w));
+    }
+  };
+  uint32_t boff[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (wave * 4 + i) * 4 + (lane >> 4);
+    const int x = (((lane & 15) >> 2) ^ (r & 3)) * 32 + (lane & 3) * 8;
+    boff[i] = x < nq ? (uint32_t)((r * ldb + x) * 2) : kOOB;
+  }
+  auto request = [&](char* b, int c) {
+    const int nr = nr_of(c);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rb, (__attribute__((address_space(3))) void*)(b + (wave * 4 + i) * 1024), 16,
+          (wave * 4 + i) * 4 + (lane >> 4) < nr ? boff[i] : kOOB, nr ? (uint32_t)(c * BR * ldb * 2) : 0u,
+          0, 0);
+  };
+
+  wfloatx16_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.f;
+  struct Frags {
+    wbf16x8_t a[2], b[2];
+  };
+  Frags f[2];
+  auto read = [&](Frags& d, const char* a, const char* b, int k) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) d.a[i] = wfrag(a, wp * 64 + i * 32, k, lane);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) d.b[j] = wfrag(b, wq * 64 + j * 32, k, lane);
+  };
+  auto mfma = [&](const Frags& d) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d.a[i], d.b[j], acc[i][j], 0, 0, 0);
+  };
+  auto sched = [&]() {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+      __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Chunk c is in (a, b); chunk c+1's X is on its way to bn, its dZ in reg.
+  auto chunk = [&](char* a, char* b, char* an, char* bn, int c) {
+    read(f[1], a, b, 1);
+    put(an, 0), put(an, 1), put(an, 2);
+    mfma(f[0]);
+    sched();
+    read(f[0], a, b, 2);
+    put(an, 3), put(an, 4), put(an, 5);
+    mfma(f[1]);
+    sched();
+    read(f[1], a, b, 3);
+    put(an, 6), put(an, 7);
+    load(c + 2);
+    mfma(f[0]);
+    sched();
+    // every load but the 8 just issued (X of chunk c+1 among them) and all LDS accesses done
+    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    request(b, c + 2);
+    read(f[0], an, bn, 0);
+    mfma(f[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  load(0);
+  request(sb0, 0);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) put(sa0, i);
+  request(sb1, 1);
+  load(1);
+  if (BF) opt_prepare(ea.opt);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  read(f[0], sa0, sb0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int c = 0; c < nch; c += 2) {   // (a chunk past the end is zeros)
+    chunk(sa0, sb0, sa1, sb1, c);
+    chunk(sa1, sb1, sa0, sb0, c + 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+
+  if (ea.with_db && ty == 0) {
+    // bias gradient: the threads' column sums, added in thread order
+    float* red = reinterpret_cast<float*>(sa0);   // [8][128]
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[ar * WT + ax + k] = dbs[k];
+    __syncthreads();
+    if (tid < WT && tid < np) {
+      float s = red[tid];
+#pragma unroll
+      for (int g = 1; g < 8; ++g) s = __fadd_rn(s, red[g * WT + tid]);
+      bias_epilogue<EPI>(ea, p0 + tid, s);
+    }
+  }
+
+  // Epilogue from the accumulators, as above.
+  const int c32 = lane & 31, r4 = (lane >> 5) * 4;
+  const int prow = p0 + wp * 64, qcol = q0 + wq * 64;
+  const int nrow = min(64, pr.P - prow), ncol = min(64, pr.Q - qcol);
+  if (nrow <= 0 || ncol <= 0) return;
+  const int64_t ld = ea.ldo;
+  const int64_t org = (int64_t)prow * ld + qcol;
+  const int64_t end = (int64_t)(nrow - 1) * ld + ncol;
+  auto desc = [&](const float* t) { return make_rsrc(t ? t + org : nullptr, t ? (int)(end * 4) : 0); };
+  const bool two = ea.opt.kind != OF_OPT_SGD;
+  const rsrc_t ro = desc(BF ? ea.W.w : ea.out);
+  const rsrc_t rm = BF ? desc(ea.W.m) : ro, rv = BF ? desc(two ? ea.W.v : nullptr) : ro;
+  const rsrc_t rg = BF ? desc(ea.gW) : ro;
+  const rsrc_t rs = BF && ea.W.w_bf16 ? make_rsrc(ea.W.w_bf16 + org, (int)(end * 2)) : ro;
+  auto at = [&](int t, int k) -> uint32_t {   // element of register k of block t = 2 i + j
+    const int col = (t & 1) * 32 + c32;
+    return col < ncol ? (uint32_t)(((t >> 1) * 32 + (k >> 2) * 8 + r4 + (k & 3)) * ld + col) : kOOB / 4;
+  };
+  float w[2][16], m[2][16], v[2][16];
+  auto fetch = [&](int t) {
+    if constexpr (BF) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        w[t & 1][k] = bload1(ro, at(t, k) * 4);
+        m[t & 1][k] = bload1(rm, at(t, k) * 4);   // no m: 0
+        v[t & 1][k] = bload1(rv, at(t, k) * 4);
+      }
+    }
+  };
+  const bool pair = BF && ea.W.w_bf16 && ld % 2 == 0 && ((uintptr_t)ea.W.w_bf16 & 3u) == 0 &&
+                    (ncol & 1) == 0;
+  auto st = [&](const rsrc_t& r, uint32_t off, float x) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, off, 0, 0);
+  };
+  fetch(0);
+  auto block = [&](auto T_) {
+    constexpr int t = decltype(T_)::value;
+    if constexpr (t + 1 < 4) fetch(t + 1);
+    float g[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) g[k] = acc[t >> 1][t & 1][k];
+    if (BF ? ea.gW != nullptr : ea.accumulate != 0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) g[k] = __fadd_rn(bload1(rg, at(t, k) * 4), g[k]);
+    }
+    if constexpr (!BF) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) st(ro, at(t, k) * 4, g[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        opt_update(ea.opt, w[t & 1][k], g[k], m[t & 1][k], v[t & 1][k]);
+        st(ro, at(t, k) * 4, w[t & 1][k]);
+        st(rm, at(t, k) * 4, m[t & 1][k]);   // no m: dropped
+        if (two) st(rv, at(t, k) * 4, v[t & 1][k]);
+      }
+      if (pair) {   // lanes 2l and 2l+1 trade a value: two columns of a row each
+        const bool odd = lane & 1;
+#pragma unroll
+        for (int k = 0; k < 16; k += 2) {
+          const float mine = odd ? w[t & 1][k + 1] : w[t & 1][k], give = odd ? w[t & 1][k] : w[t & 1][k + 1];
+          const float got = __int_as_float(
+              __builtin_amdgcn_mov_dpp(__float_as_int(give), 0xb1, 0xf, 0xf, true));
+          const uint32_t e = at(t, k);
+          __builtin_amdgcn_raw_buffer_store_b32(odd ? cvt2(got, mine) : cvt2(mine, got), rs,
+                                                e == kOOB / 4 ? kOOB : (e + (odd ? (uint32_t)ld - 1u : 0u)) * 2u,
+                                                0, 0);
+        }
+      } else if (ea.W.w_bf16) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+          __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(w[t & 1][k]), rs,
+                                                at(t, k) == kOOB / 4 ? kOOB : at(t, k) * 2u, 0, 0);
+      }
+    }
+  };
+  each(std::make_integer_sequence<int, 4>{}, block);
+}
+
+hipError_t wgrad_bf16_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, hipStream_t s) {
+  const dim3 g((pr.P + WT - 1) / WT, (pr.Q + WT - 1) / WT);
+  if (kind == EPI_WGRAD) hipLaunchKernelGGL((wgrad_bf16_kernel<EPI_WGRAD>), g, dim3(256), 0, s, pr, ea);
+  else if (kind == EPI_WGRAD_BF) hipLaunchKernelGGL((wgrad_bf16_kernel<EPI_WGRAD_BF>), g, dim3(256), 0, s, pr, ea);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 template <int EPI, bool A32, int ACT>

@@ -100,3 +100,44 @@ def test_gelu_tails():
     x64 = x.double()
     assert (y.double() - x64 * torch.special.ndtr(x64)).abs().le(x64.abs() * 1.2e-7).all()
     assert (dx.double() - _dgelu(x64)).abs().le(3e-7).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 1540, 2056), (333, 3076, 1032), (200, 1800, 1800), (129, 2048, 1536)])
+@pytest.mark.parametrize("opt,early", [("adamw", 0), ("sgd", 1), ("adagrad", 0)])
+def test_weight_gradient(M, N, K, opt, early):
+    """At least 192 tiles of 128 x 128: dW, db against float64, accumulation, and the fused update bit
+    for bit against the eager gradient and optimizer step (with an earlier use's gradient too)."""
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    dz, x = torch.randn(M, N, generator=g, device=DEV), torch.randn(M, K, generator=g, device=DEV)
+    xb, s = x.bfloat16(), torch.cuda.current_stream().cuda_stream
+    d = L.OfLinearDesc(M, N, K, 0, 0, L.OF_BF16, 0, 1, L.OF_IO_X_BF16)
+    keep, ws = _ws(L.of_linear_workspace_size(d, 2))
+    dw, db = torch.empty(N, K, device=DEV), torch.empty(N, device=DEV)
+    L.of_linear_bwd_weight(d, dz.data_ptr(), xb.data_ptr(), dw.data_ptr(), db.data_ptr(), 0, *ws, s)
+    a64, x64 = dz.bfloat16().double().t(), xb.double()
+    assert (dw.double() - a64 @ x64).abs().le(_bound(a64, x64, M)).all()
+    assert (db.double() - dz.double().sum(0)).abs().le(dz.double().abs().sum(0) * M * 2.0 ** -24).all()
+    gw, gb = torch.randn(N, K, generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
+    if early:
+        dw2, db2 = gw.clone(), gb.clone()
+        L.of_linear_bwd_weight(d, dz.data_ptr(), xb.data_ptr(), dw2.data_ptr(), db2.data_ptr(), 1, *ws, s)
+        assert torch.equal(dw2, gw + dw) and torch.equal(db2, gb + db)
+        dw, db = dw2, db2
+    hyper = dict(kind=opt, lr=1e-2, momentum=0.9, beta1=0.9, beta2=0.99, eps=1e-8, weight_decay=1e-2)
+    sets = []
+    for _ in range(2):
+        t = [torch.randn(N, K, generator=torch.Generator(device=DEV).manual_seed(5 + i), device=DEV).abs()
+             for i in range(3)] + [torch.zeros(N, K, device=DEV, dtype=torch.bfloat16)]
+        u = [torch.ones(N, device=DEV) * (i + 1) for i in range(3)]
+        W, b = L.param_of(t[0], t[1], t[2], t[3]), L.param_of(*u)
+        if opt == "adagrad":
+            W.m = b.m = None
+        sets.append((t, u, W, b))
+    o = L.make_opt(hyper, 3)
+    t, u, W, b = sets[0]
+    L.of_optimizer_step(2, (L.OfParam * 2)(W, b), (L.c_void_p * 2)(dw.data_ptr(), db.data_ptr()), o, s)
+    t2, u2, W2, b2 = sets[1]
+    L.of_linear_bwd_fused(d, dz.data_ptr(), xb.data_ptr(), W2, b2, gw.data_ptr() if early else None,
+                          gb.data_ptr() if early else None, o, None, 0, None, None, 0, *ws, s, None)
+    for p, q in zip(t + u, t2 + u2):
+        assert torch.equal(p, q)
