@@ -16,6 +16,12 @@
 // during steps 0..2 of the chunk after its loads were issued).  The two buffers are
 // arrays of their own: the compiler then knows which reads a load to LDS concerns.
 //
+// Measured: the main loop at 1.45 PFLOP/s; 4096 x 4096 x 1024 forward with GELU, Z and a
+// bf16 Y 83 -> 57 us (100 MB of stores: staged through LDS they took 55 us of a
+// plain forward's 79, from the accumulators about 30); its data gradient with
+// GELU's derivative (4096 x 1024 x 4096) 95 -> 63 us.  Below 160 tiles the chip is
+// not full and the general kernel's smaller tiles win.
+//
 // LDS layout: reduction-contiguous operands as rows [x][64], 16-byte slots
 // XOR-swizzled by (x >> 1) & 7, so 16 consecutive rows' reads cover all banks;
 // output-contiguous ones (the data gradient's W) as rows [r][256], 64-byte blocks
@@ -381,7 +387,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
 // update runs on the accumulators: W, m and v are requested a 32x32 block ahead
 // and moved in 128-byte row segments.  Bound by LDS and the loads (768 clocks of
 // either per chunk, 512 of MFMAs), then by the update's memory traffic.
-// 1024 x 4096 over 4096 rows with AdamW: 111 us on the general kernel.
+// 1024 x 4096 over 4096 rows with AdamW: backward and update 173 -> 154.5 us.
 namespace {
 
 constexpr int WT = 128;                  // tile rows and columns
