@@ -89,11 +89,11 @@ using T256x32 = Tile<256, 32, 16, 4, 1, 1, 3>;
 enum TileId {
   TI_32x32 = 0, TI_64x32, TI_64x64, TI_128x64, TI_128x128, TI_256x32,
   TI_32x32D, TI_32x32D8,
-  TI_S128x128, TI_S64x128, TI_S64x64, TI_S64x32, TI_COUNT
+  TI_S128x128, TI_S64x128, TI_S64x64, TI_S64x32, TI_S128x32, TI_S128x32N, TI_S128x32R, TI_COUNT
 };
-static const int kTileBP[TI_COUNT] = {32, 64, 64, 128, 128, 256, 32, 32, 128, 64, 64, 64};
-static const int kTileBQ[TI_COUNT] = {32, 32, 64, 64, 128, 32, 32, 32, 128, 128, 64, 32};
-static const int kTileBR[TI_COUNT] = {32, 32, 16, 16, 16, 16, 32, 32, 16, 32, 32, 32};
+static const int kTileBP[TI_COUNT] = {32, 64, 64, 128, 128, 256, 32, 32, 128, 64, 64, 64, 128, 128, 128};
+static const int kTileBQ[TI_COUNT] = {32, 32, 64, 64, 128, 32, 32, 32, 128, 128, 64, 32, 32, 32, 32};
+static const int kTileBR[TI_COUNT] = {32, 32, 16, 16, 16, 16, 32, 32, 16, 32, 32, 32, 32, 32, 32};
 
 
 // -------------------------------------------------------------------- kernel
@@ -669,33 +669,46 @@ static int ff_tile(int P) { return P <= 32 ? TI_32x32 : TI_64x32; }
 // The tile and split of least cost among the tiles that run on the bf16 matrix
 // cores, in us: a workgroup alone multiplies at `rate` TFLOP/s, `conc` workgroups
 // share a CU without slowing each other, and a split adds a second pass (a
-// fixed cost plus writing and reading the partials).  Over the chip that is
-// 175 TFLOP/s for 128x128, 160 for 64x128, and for 64x64 90 with one workgroup
-// per CU and 138 with two (measured at 1024 x 2048 x 2048 and up).
+// fixed cost plus writing and reading the partials).  Fitted to 3500 times of every
+// tile with 1 to 32 splits, at 0.6 GFLOP to 40 GFLOP; what it picks takes 1% (linear)
+// to 2% (convolutions) more than the best of them, 4% to 6% where an operand takes
+// single loads.  Over the chip aligned linear products reach 131 TFLOP/s (1024 x
+// 2048 x 2048).
+//
 // A weight gradient has no 64x128 tile (its transposing reads of both operands
-// leave no registers for it), and unsplit it takes 64x64: backward-fusion's
+// leave no registers for it), and its whole reductions take 64x64: backward-fusion's
 // update of a 128x128 tile leaves a CU's one workgroup waiting for W, m and v
-// (fused / plain, 64 x 8192 x 8192: 364 / 100 us on 128x128, 322 / 115 on 64x64;
-// 1024 x 2048 x 2048: 75 / 51, 67 / 60).
-static GemmCfg cheapest_split(int kind, int P, int Q, int R) {
-  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
-  struct { int t; double rate, conc; } const tiles[3] = {
-      {TI_S128x128, 0.69, 1.0}, {TI_S64x128, kind == EPI_DGRAD ? 0.50 : 0.63, 1.0},
-      {TI_S64x64, 0.38, 1.5}};
+// (fused / plain, 64 x 8192 x 8192: 396 / 104 us on 128x128, 350 / 129 on 64x64;
+// 128 x 4096 x 4096: 95 / 41, 80 / 48).  With single loads 128x128 wins both ways
+// (64 x 8190 x 8190: 641 / 155 us, 785 / 196).  A convolution's gathers with single
+// loads spill on 64x128, and in a weight gradient on 128x128, so these are left out.
+static GemmCfg cheapest_split(int kind, int P, int Q, int R, int conv) {
+  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF, fwd = kind == EPI_FWD || kind == EPI_FWD_FF;
+  const bool vec = (wg ? P : R) % 4 == 0 && (fwd ? R : Q) % 4 == 0;   // whole float4s
+  struct Cost { int t; double rate, conc; };
+  static const Cost kLinear[3] = {{TI_S128x128, 0.66, 1.0}, {TI_S64x128, 0.61, 1.0}, {TI_S64x64, 0.52, 1.25}};
+  static const Cost kSingle[3] = {{TI_S128x128, 0.52, 1.0}, {TI_S64x128, 0.53, 1.0}, {TI_S64x64, 0.37, 1.0}};
+  static const Cost kSingleW[3] = {{TI_S128x128, 0.73, 1.0}, {TI_S64x128, 0.0, 1.0}, {TI_S64x64, 0.26, 1.0}};
+  static const Cost kConvW[3] = {{TI_S128x128, 0.40, 1.5}, {TI_S64x128, 0.0, 1.0}, {TI_S64x64, 0.25, 3.0}};
+  static const Cost kConv[3] = {{TI_S128x128, 0.61, 1.5}, {TI_S64x128, 0.49, 1.3}, {TI_S64x64, 0.385, 1.6}};
+  const Cost* tiles = conv ? (wg && Q % 4 == 0 ? kConvW : kConv) : vec ? kLinear : wg ? kSingleW : kSingle;
+  const double second = conv ? 2.3 : 5.0;
   double best = 1e30;
   GemmCfg pick{TI_S64x64, 1, (R + 31) / 32 * 32};
-  for (const auto& c : tiles) {
-    if (wg && c.t == TI_S64x128) continue;
+  for (int i = 0; i < 3; ++i) {
+    const Cost& c = tiles[i];
+    if (c.t == TI_S64x128 && (wg || (conv && !vec))) continue;
+    if (c.t == TI_S128x128 && wg && conv && !vec) continue;
     const int BR = kTileBR[c.t];
     for (int S = 1; S <= 64; S *= 2) {
       if (S > 1 && R / S < 4 * BR) continue;
       const int r_split = ((R + S - 1) / S + BR - 1) / BR * BR;
       const int Se = (R + r_split - 1) / r_split;
-      if (wg && Se == 1 && c.t == TI_S128x128) continue;
+      if (wg && Se == 1 && c.t == TI_S128x128 && vec) continue;
       const double W = (double)ntiles(c.t, P, Q) * Se;
       double T = 2e-6 * kTileBP[c.t] * kTileBQ[c.t] * r_split / c.rate *
                  std::max(1.0, W / (256.0 * c.conc));
-      if (Se > 1) T += 5.0 + (double)P * Q * Se * 8 / 5e6;
+      if (Se > 1) T += second + (double)P * Q * Se * 8 / 4.9e6;
       if (T < best) {
         best = T;
         pick = GemmCfg{c.t, Se, r_split};
@@ -705,15 +718,27 @@ static GemmCfg cheapest_split(int kind, int P, int Q, int R) {
   return pick;
 }
 
-// Whether a linear layer's contraction has enough work for those tiles to beat
-// the fp32 ones.  Measured on MI355X, fp32 / bf16 matrix cores: 256 x 1024 x 1024
-// forward 10.6 / 13.5 us, weight gradient 10.2 / 9.2 (fused 13.6 / 13.7, and 2% of an
-// 8-layer step lost); 512 x 1024 x 1024 forward 18.9 / 18.0, data gradient 16.0 / 18.0,
-// weight gradient 14.9 / 13.5 (fused 20.7 / 18.3); 1000 x 1024 x 1024 30.1 / 25.9, 27.4 /
-// 22.2, 25.1 / 23.0; 1024 x 2048 x 2048 86 / 58, 86 / 60, fused 98 / 67.
-static bool split_pays(int kind, int P, int Q, int R) {
-  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
-  return P > 32 && Q > 32 && R >= 64 && 2.0 * P * Q * R >= (wg ? 8e8 : 1.2e9);
+// Whether a linear layer's contraction gains from those tiles (their choice c) over
+// the fp32 ones.  Measured on MI355X, fp32 / bf16 matrix cores, us: forward 512 x
+// 1024 x 1024 18.1 / 18.6, 1024 x 1024 x 1024 28 / 25, 1024 x 2048 x 2048 79 / 66; data
+// gradient 512 x 1024 x 1024 15.6 / 18.6, 2048 x 512 x 768 22.1 / 18.9, 1024 x 2048 x 2048
+// 78 / 69; weight gradient 512 x 1024 x 1024 18.0 / 14.1 (fused 20.2 / 19.2), 1024 x 2048 x
+// 2048 84 / 70 (95 / 80).  A reduction split in two pays later (forward 640 x 1000 x 1004
+// 20.2 / 22.7), a data gradient on few tiles too (768 x 1024 x 1024 21.4 / 22.8), and so do a data gradient of
+// at most 64 rows (64 x 4096 x 4096 26.0 / 27.4; 40 x 4096 x 8192 41.5 / 38.8) and a weight
+// gradient with single loads over a short reduction (577 x 1033 x 1031 34.8 / 38.7,
+// 900 x 1033 x 1031 52 / 48; 1001 x 801 x 903 38 / 34).
+static bool split_pays(int kind, int P, int Q, int R, const GemmCfg& c) {
+  const double flops = 2.0 * P * Q * R;
+  if (P <= 32 || Q <= 32 || R < 64) return false;
+  if (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) {
+    const bool vec = P % 4 == 0 && Q % 4 == 0;
+    return flops >= (!vec && R <= 1000 ? 1.6e9 : 8e8);
+  }
+  if (kind == EPI_DGRAD && P <= 64) return flops >= 2.5e9;
+  if (c.S == 2 || (kind == EPI_DGRAD && c.S == 1 && ntiles(c.tile, P, Q) < 224))
+    return flops >= (kind == EPI_DGRAD ? 1.7e9 : 1.3e9);
+  return flops >= 1.2e9;
 }
 
 static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
@@ -736,7 +761,8 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
   }
   if (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) {
     // (A very long reduction onto few outputs stays on the narrow fp32 tiles below.)
-    if (R < 65536 && split_pays(kind, P, Q, R)) return cheapest_split(kind, P, Q, R);
+    const GemmCfg c = cheapest_split(kind, P, Q, R, 0);
+    if (R < 65536 && split_pays(kind, P, Q, R, c)) return c;
     if (R <= 1024 && ntiles(TI_32x32, P, Q) >= 512) return make_cfg(TI_32x32, P, Q, R, 1, 1);
     // A very long reduction onto few outputs (the pixel rows of a 1x1
     // convolution, 65k-400k rows onto a few hundred weights): up to 256
@@ -760,7 +786,8 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
       return make_cfg(P >= 65536 ? TI_256x32 : (Q <= 32 ? TI_32x32 : TI_64x64), P, Q, R, 1, 1);
     return make_cfg(Q <= 32 ? TI_64x32 : TI_64x64, P, Q, R, 1, 1);
   }
-  if (split_pays(kind, P, Q, R)) return cheapest_split(kind, P, Q, R);
+  const GemmCfg c = cheapest_split(kind, P, Q, R, 0);
+  if (split_pays(kind, P, Q, R, c)) return c;
   if (P <= 64 && ntiles(TI_64x64, P, Q) >= 64) return make_cfg(TI_64x64, P, Q, R, 1024, 8);
   // Larger outputs: the biggest tile that still gives one workgroup per CU; no
   // reduction split (each split costs a second kernel, ~4 us back to back).
@@ -802,8 +829,14 @@ static GemmCfg select_cfg_conv(int kind, int P, int Q, int R) {
   if (Q <= 32 && P <= 32 && R >= 65536) return make_cfg(TI_32x32, P, Q, R, 256, 256);
   // Enough work for the tiles on the bf16 matrix cores (measured on MI355X, fp32 /
   // bf16 matrix cores, forward, data and weight gradient: 128 x 8 x 8 x 256 -> 256
-  // 100 / 62, 106 / 69, 106 / 80 us; 16 x 14 x 14 x 96 -> 160 23 / 19, 25 / 20, 23 / 19).
-  if (P > 32 && Q > 32 && R >= 64 && 2.0 * P * Q * R >= 5e8) return cheapest_split(kind, P, Q, R);
+  // 97 / 76, 103 / 76, 105 / 92 us; 16 x 14 x 14 x 96 -> 160 23 / 19, 25 / 20, 23 / 20).
+  // A weight gradient that gathers single channels (C % 4 != 0, Q = 9 C) does so for
+  // every 64 output channels there; fp32 tiles win from 4 GFLOP (128 x 8 x 8 x 255 ->
+  // 257 182 / 184, x 254 -> 256 137 / 131; 64 x 15 x 16 x 99 -> 100, 2.7 GFLOP, 57 / 50).
+  const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
+  const double flops = 2.0 * P * Q * R;
+  if (P > 32 && Q > 32 && R >= 64 && flops >= 5e8 && !(wg && Q % 4 != 0 && flops >= 4e9))
+    return cheapest_split(kind, P, Q, R, 1);
   static const double kEff[6] = {0.489, 0.283, 0.617, 0.488, 0.714, 0.765};
   static const int kConc[6] = {1, 4, 3, 4, 2, 1};
   static const int kSplits[8] = {1, 2, 4, 8, 16, 32, 64, 128};
@@ -1002,10 +1035,12 @@ hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, vo
   // forward given it takes 128x64 with the same splits (the same reduction
   // ranges and workspace).
   if (kind == EPI_FWD_FF && c.tile == TI_128x128) c.tile = TI_128x64;
-  // The fused forward's registers hold W, g, m and v, so it takes smaller tiles
-  // with the same splits and, per output element, the same MFMA sequence.
-  if (kind == EPI_FWD_FF && c.tile == TI_S128x128) c.tile = TI_S64x64;
-  if (kind == EPI_FWD_FF && c.tile == TI_S64x128) c.tile = TI_S64x32;
+  // The fused forward takes narrower tiles with the same splits and, per output
+  // element, the same MFMA sequence.
+  if (kind == EPI_FWD_FF && c.tile == TI_S128x128) c.tile = TI_S128x32;
+  if (kind == EPI_FWD_FF && c.tile == TI_S64x64) c.tile = TI_S128x32N;
+  // (300 x 3000 x 3000: 174 us on 64x32, 204 on 128x32R; 4095 x 999 x 1001: 402, 308)
+  if (kind == EPI_FWD_FF && c.tile == TI_S64x128) c.tile = pr.P <= 512 ? TI_S64x32 : TI_S128x32R;
   EpiArgs ea = ea_in;
   ea.carry.cz = 0;
   if (ea.carry.t[0].p.w) {

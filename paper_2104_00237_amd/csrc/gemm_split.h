@@ -1,32 +1,34 @@
 // fp32 contractions on the bf16 matrix cores, for products large enough that
 // the matrix cores bound them.
 //
-// Every fp32 operand x is split exactly into three bf16 values by truncation,
+// Every fp32 operand x is split into three bf16 values by truncation,
 //   x = h + m + l,  h = x's top 8 significant bits, m the next 8, l the last 8,
-// and a product a*b is summed as the six partial products of weight 2^-16 or
-// more relative to it,
-//   ah*bh  +  (ah*bm + am*bh + am*bm + ah*bl + al*bh);
-// the three left out (am*bl, al*bm, al*bl) are below 2^-23 of it, under the
-// rounding of an fp32 product sum.  Products of bf16 values are exact in fp32
-// and v_mfma_f32_32x32x16_bf16 accumulates in fp32; the leading products and the
-// corrections have accumulators of their own, added once at the end.  Six such
-// MFMAs cover 16 reduction elements in 192 cycles; v_mfma_f32_32x32x2_f32 needs 512.
+// exactly down to 2^-110; below, bits under the smallest bf16 (2^-133) are lost.
+// A product a*b is summed as eight partial products,
+//   ah*bh  +  (am*bl + al*bm + al*bh + ah*bl + am*bm + am*bh + ah*bm);
+// the ninth, al*bl, is below 2^-29 of it.  (Truncated parts have the operand's sign:
+// leaving out am*bl and al*bm too, each below 2^-22, would make every product too
+// small by up to 2^-21, eight roundings of an fp32 product.)  Products of bf16
+// values are exact in fp32 and v_mfma_f32_32x32x16_bf16 accumulates in fp32; the
+// leading products and the corrections have accumulators of their own, added once
+// at the end, so a sum of one product is rounded once.  Eight such MFMAs cover 16
+// reduction elements in 256 cycles; v_mfma_f32_32x32x2_f32 needs 512.
 //
 // Infinities and NaN: h of an infinite element is infinite and its m is NaN, so
 // the corrections it touches become NaN, while the leading sum holds what the
 // fp32 sum would; a leading sum that is not finite is therefore the result by
 // itself.  h never rounds up, so the largest finite values stay finite.
 //
-// What bounds it: on a full chip the MFMAs alone run at 285 TFLOP/s of fp32
-// products (1.7 PFLOP/s of bf16), with the operand reads from LDS too; splitting
-// (5.5 vector instructions per element) and staging bring that to 214, the
-// global loads to 177 (2048 x 4096 x 4096; fp32 MFMA tiles: 97).  A 64x64 sub-tile
-// per wavefront keeps LDS reads at half its bandwidth; two workgroups per CU
-// fill each other's issue slots, and one alone does nearly as well when the
-// split and the loads are spread between its MFMAs (sched_group_barrier).  A
-// third LDS buffer with one wavefront per SIMD (operands of the next step
-// read ahead) was slower: 154 against 172 TFLOP/s at 256 workgroups.  Errors against
-// float64 are a third of the fp32 MFMA tiles' (1024 x 2048 x 2048 forward 1.9e-7, 5.5e-7).
+// What bounds it: the MFMAs (half of an fp32 MFMA's time: 314 TFLOP/s at the peak
+// clock), the split (5.5 vector instructions per element) and staging between them,
+// and the global loads: 168 TFLOP/s at 2048 x 4096 x 4096 (409 us; fp32 MFMA tiles
+// 526, 131).  A 64x64 sub-tile per wavefront keeps LDS reads at half its bandwidth;
+// two workgroups per CU fill each other's issue slots, and one alone does nearly as
+// well when the split and the loads are spread between its MFMAs
+// (sched_group_barrier).  A third LDS buffer with one wavefront per SIMD (operands of
+// the next step read ahead) was slower by a tenth.  Errors against float64, split and
+// fp32 MFMA tiles: 1024 x 2048 x 2048 forward 1.3e-7, 8.1e-7; outputs of one product
+// 2.5e-8 both, of 8 products 2.8e-8, 5.4e-8.
 //
 // LDS: each operand tile is three planes (h, m, l) of bf16 in the operand's
 // memory order.  Reduction-contiguous: rows [x][BR], whose 16-byte slots are
@@ -48,9 +50,10 @@ typedef __bf16 sbf16x8_t __attribute__((ext_vector_type(8)));
 typedef short sshort4_t __attribute__((ext_vector_type(4)));
 typedef float sfloatx16_t __attribute__((ext_vector_type(16)));
 
-template <int BP_, int BQ_, int BR_, int WP_, int WQ_, int WR_, int NS_>
+template <int BP_, int BQ_, int BR_, int WP_, int WQ_, int WR_, int NS_, int NA_ = 1>
 struct STile {
   static constexpr int BP = BP_, BQ = BQ_, BR = BR_, WP = WP_, WQ = WQ_, WR = WR_, NS = NS_;
+  static constexpr int NA = NA_;   // leading sums per output element (see S64x64)
   static_assert(WP * WQ * WR == 4, "a workgroup is 4 wavefronts");
   static constexpr int WTP = BP / WP, WTQ = BQ / WQ;
   static constexpr int TP = WTP / 32, TQ = WTQ / 32;
@@ -59,15 +62,25 @@ struct STile {
   static_assert(RW % 16 == 0 && (BR == 16 || BR == 32), "whole MFMA steps");
 };
 
-// 128x128 and 64x128: a 64x64 sub-tile per wavefront, 12 KB of LDS reads per 24
+// 128x128 and 64x128: a 64x64 sub-tile per wavefront, 12 KB of LDS reads per 32
 // MFMAs; in the 64-row tile two wavefronts halve each chunk's reduction and
-// their sums are added in wave order.  64x64: 32x32 sub-tiles, for outputs too
-// small for the others.
+// their sums are added in wave order.  64x64: 32x32 sub-tiles, for smaller outputs;
+// its registers hold four leading sums per element (two for gradients, whose
+// transposing reads need more), which take the reduction steps in turn: rounding
+// errors grow with the length of a chain (1000 x 1024 x 1024 forward: 1.8e-7 with one,
+// 1.0e-7 with four).
 using S128x128 = STile<128, 128, 16, 2, 2, 1, 2>;
 using S64x128 = STile<64, 128, 32, 1, 2, 2, 2>;
-using S64x64 = STile<64, 64, 32, 2, 2, 1, 2>;
-// The fused forward of at most 64 rows: the reduction layout of 64x128, so every
-// output element takes the same MFMA sequence as in the plain forward.
+using S64x64 = STile<64, 64, 32, 2, 2, 1, 2, 4>;
+// The fused forward's tiles: W, g, m and v take registers, so they are narrow.
+// 128x32 stands for 128x128, 128x32N for 64x64, 128x32R and 64x32 (up to 512 rows) for
+// 64x128: whole or halved chunks and leading sums as there, so every output element
+// takes the same MFMA sequence as in the plain forward.  With as many columns as
+// the plain tiles too few wavefronts fit (1000 x 1024 x 1024: 88 us on 64x64, 60 on
+// 128x32; 512 x 4096 x 4096: 370 us with a 128x64 tile, 275).
+using S128x32 = STile<128, 32, 32, 4, 1, 1, 2>;
+using S128x32N = STile<128, 32, 32, 4, 1, 1, 2, 4>;
+using S128x32R = STile<128, 32, 32, 2, 1, 2, 2>;
 using S64x32 = STile<64, 32, 32, 2, 1, 2, 2>;
 
 // A float4 as three 8-byte quads of bf16.
@@ -199,13 +212,18 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmProblem pr, EpiA
   const bool do_db = WG && ea.with_db && ty == 0;
   const bool ff_owner = ea.Wout.w == nullptr || p0 == 0;
 
-  sfloatx16_t acc[T::TP][T::TQ], cor[T::TP][T::TQ];
+  constexpr int NA = T::NA == 1 || (A_RC && B_RC) ? T::NA : 2;
+  sfloatx16_t acc[NA][T::TP][T::TQ], cor[T::TP][T::TQ];
 #pragma unroll
   for (int i = 0; i < T::TP; ++i)
 #pragma unroll
     for (int j = 0; j < T::TQ; ++j)
 #pragma unroll
-      for (int k = 0; k < 16; ++k) acc[i][j][k] = cor[i][j][k] = 0.f;
+      for (int k = 0; k < 16; ++k) {
+        cor[i][j][k] = 0.f;
+#pragma unroll
+        for (int n = 0; n < NA; ++n) acc[n][i][j][k] = 0.f;
+      }
 
   constexpr int NS = T::NS;   // chunks in the register ring
   using ALoad = std::conditional_t<
@@ -297,7 +315,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmProblem pr, EpiA
   auto chunk = [&](const int c, const int s) {
     Frags f[T::KS];
     constexpr int RA = A_RC ? 1 : 2, RB = B_RC ? 1 : 2;          // LDS reads per operand
-    constexpr int NM = 6 * T::KS * T::TP * T::TQ;                // MFMAs per chunk
+    constexpr int NM = 8 * T::KS * T::TP * T::TQ;                // MFMAs per chunk
     constexpr int R0 = T::TP * RA + T::TQ * RB, NRD = 3 * T::KS * R0;
 #pragma unroll
     for (int k = 0; k < T::KS; ++k) read(f[k], c, k);
@@ -307,7 +325,9 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmProblem pr, EpiA
     stage_b((s + 1) % NS, c + 1);
 #pragma unroll
     for (int k = 0; k < T::KS; ++k) {
-      mm(acc, f[k], 0, 0);
+      mm(acc[(s * T::KS + k) % NA], f[k], 0, 0);
+      mm(cor, f[k], 2, 1);
+      mm(cor, f[k], 1, 2);
       mm(cor, f[k], 2, 0);
       mm(cor, f[k], 0, 2);
       mm(cor, f[k], 1, 1);
@@ -318,7 +338,9 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmProblem pr, EpiA
       // after the first operands: one MFMA, then its share of the LDS reads, of
       // the loads, of the split's vector instructions and of the LDS stores
       constexpr int NEL = (T::BP + T::BQ) * T::BR / 1024;         // float4s split per chunk
-      constexpr int NV = (NEL * 26 + NM - 1) / NM;
+      // (26 vector instructions split and pack a float4; four single loads in its
+      // place need 16 more for their addresses)
+      constexpr int NV = (NEL * (VECS == 3 ? 26 : 42) + NM - 1) / NM;
       __builtin_amdgcn_sched_group_barrier(0x100, R0, 0);
 #pragma unroll
       for (int g = 0; g < NM; ++g) {
@@ -373,7 +395,10 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmProblem pr, EpiA
         for (int k = 0; k < 16; ++k) {
           const int p = wp * T::WTP + i * 32 + (k >> 2) * 8 + (lane >> 5) * 4 + (k & 3);
           const int q = wq * T::WTQ + j * 32 + (lane & 31);
-          Cs[(wr * PR + p) * LDC + q] = split_sum(acc[i][j][k], cor[i][j][k]);
+          float hh = acc[0][i][j][k];
+#pragma unroll
+          for (int n = 1; n < NA; ++n) hh = __fadd_rn(hh, acc[n][i][j][k]);
+          Cs[(wr * PR + p) * LDC + q] = split_sum(hh, cor[i][j][k]);
         }
     __syncthreads();
     auto item = [&](int idx, float (&c)[4]) {   // results of item idx of the band
@@ -511,6 +536,6 @@ static hipError_t split_launch_t(int S, int cz, int r_split, const GemmProblem& 
   return hipGetLastError();
 }
 
-enum SplitTile { ST_128x128 = 0, ST_64x128, ST_64x64, ST_64x32, ST_COUNT };
+enum SplitTile { ST_128x128 = 0, ST_64x128, ST_64x64, ST_64x32, ST_128x32, ST_128x32N, ST_128x32R, ST_COUNT };
 
 }  // namespace opfuse
