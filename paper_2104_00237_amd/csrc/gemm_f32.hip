@@ -763,6 +763,11 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
     // (A very long reduction onto few outputs stays on the narrow fp32 tiles below.)
     const GemmCfg c = cheapest_split(kind, P, Q, R, 0);
     if (R < 65536 && split_pays(kind, P, Q, R, c)) return c;
+    // A short reduction onto a huge output (an 8192 x 8192 layer at fewer than 64 rows):
+    // whole reductions on 64x64 tiles (measured on MI355X, plain / fused with AdamW: 16
+    // rows 88 / 352 us, 160 / 371 on 32x32 tiles; 63 rows 123 / 359, 183 / 381; a 4096 x
+    // 4096 layer at 16 rows 21 / 66, 44 / 62, at 48 rows 30 / 70, 51 / 70).
+    if (R <= 128 && ntiles(TI_128x128, P, Q) >= 1024) return make_cfg(TI_64x64, P, Q, R, 1, 1);
     if (R <= 1024 && ntiles(TI_32x32, P, Q) >= 512) return make_cfg(TI_32x32, P, Q, R, 1, 1);
     // A very long reduction onto few outputs (the pixel rows of a 1x1
     // convolution, 65k-400k rows onto a few hundred weights): up to 256
