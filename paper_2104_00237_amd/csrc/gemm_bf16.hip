@@ -482,7 +482,7 @@ static int64_t bntiles(int t, int P, int Q) {
   return (int64_t)((P + kBTileBP[t] - 1) / kBTileBP[t]) * ((Q + kBTileBQ[t] - 1) / kBTileBQ[t]);
 }
 
-constexpr int64_t kWideTiles = 160, kWgradTiles = 192;   // see wide_ok, wgrad_ok
+constexpr int64_t kWideTiles = 160;   // see wide_ok
 static int64_t tiles256(int P, int Q) { return (int64_t)((P + 255) / 256) * ((Q + 255) / 256); }
 
 // 128x256 eight-wave tiles for large outputs (at least 512 of them) and, in
@@ -513,11 +513,7 @@ static BCfg bselect_default(int kind, int P, int Q, int R) {
   // Shapes that the kernels with direct loads take unsplit when the operands'
   // storage and alignment allow: the same order of sums here, so that results do
   // not depend on either.
-  if (kind == EPI_FWD || kind == EPI_DGRAD) {
-    if (tiles256(P, Q) >= kWideTiles) S = 1;
-  } else if (bntiles(BTI_128x128, P, Q) >= kWgradTiles) {
-    S = 1;
-  }
+  if ((kind == EPI_FWD || kind == EPI_DGRAD) && tiles256(P, Q) >= kWideTiles) S = 1;
   int r_split = (((R + S - 1) / S) + BR - 1) / BR * BR;
   S = (R + r_split - 1) / r_split;
   return BCfg{t, S, r_split};
@@ -646,15 +642,25 @@ static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_
 
 // Whether the weight-gradient kernel with direct loads takes a weight gradient:
 // X stored as bf16 in whole 16-byte pieces, dZ in whole quads, offsets within a
-// descriptor, and enough tiles to fill the chip unsplit (192 is three quarters of
-// it: a 3072 x 1024 layer).  Outputs of 512 128x256 tiles stay on those.
+// descriptor; a 128x128 tile for every CU, which takes whole reductions, and the last
+// round of 256 tiles at least a quarter full; at least 1024 rows; and dW's rows in
+// whole 128-byte lines, which its epilogue moves.  Measured, general kernel / this one,
+// fused AdamW (plain) in us:
+//   2048 x 2048, 4096 rows 94.7 / 79.1 (79.0 / 57.5), 1024 rows with the data gradient
+//   84.3 / 80.0, 512 rows 35.9 / 39.3 (19.6 / 14.7), 90 rows with it 42.9 / 49.6;
+//   2800 x 1504 (264 tiles), 3000 rows 82.6 / 88.6 (68.3 / 62.5); 3000 x 2016 (384) 86.9 /
+//   85.6 (71.7 / 64.9);
+//   3072 x 1024 (192 tiles, split in two there), 4096 rows 68.6 / 76.2 (58.6 / 54.9);
+//   8192 x 1000 (rows of 4000 bytes), 2048 rows 80.3 / 86.9 (59.2 / 52.4).
+// Outputs of 512 128x256 tiles stay on those.
 static bool wgrad_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_ops) {
   if ((kind != EPI_WGRAD && kind != EPI_WGRAD_BF) || vec_ops != 3 || !pr.b_bf16) return false;
-  if (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0) return false;
+  if (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 32 != 0 || ea.ldo % 32 != 0) return false;
   if ((int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31) || (int64_t)pr.R * pr.a_sr * 4 >= (1LL << 31) ||
       ea.ldo > (1 << 22))
     return false;
-  return bntiles(BTI_128x128, pr.P, pr.Q) >= kWgradTiles && bntiles(BTI_128x256, pr.P, pr.Q) < 512;
+  const int64_t nt = bntiles(BTI_128x128, pr.P, pr.Q);
+  return pr.R >= 1024 && nt >= 256 && (nt - 1) % 256 >= 63 && bntiles(BTI_128x256, pr.P, pr.Q) < 512;
 }
 
 hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& ea_in, void* ws,

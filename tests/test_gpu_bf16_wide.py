@@ -102,10 +102,13 @@ def test_gelu_tails():
     assert (dx.double() - _dgelu(x64)).abs().le(3e-7).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(64, 1540, 2056), (333, 3076, 1032), (200, 1800, 1800), (129, 2048, 1536)])
+# 192 tiles of 128 x 128 and more; the last four on the kernel with direct loads: one row and one column
+# past whole chunks and tiles, an odd number of chunks, the fewest rows
+@pytest.mark.parametrize("M,N,K", [(64, 1540, 2056), (333, 3076, 1032), (200, 1800, 1800), (129, 2048, 1536),
+                                   (1025, 2980, 2016), (1091, 4100, 1312), (1999, 2048, 2048), (1024, 3000, 1760)])
 @pytest.mark.parametrize("opt,early", [("adamw", 0), ("sgd", 1), ("adagrad", 0)])
 def test_weight_gradient(M, N, K, opt, early):
-    """At least 192 tiles of 128 x 128: dW, db against float64, accumulation, and the fused update bit
+    """dW, db against float64, accumulation, and the fused update bit
     for bit against the eager gradient and optimizer step (with an earlier use's gradient too)."""
     g = torch.Generator(device=DEV).manual_seed(M + N)
     dz, x = torch.randn(M, N, generator=g, device=DEV), torch.randn(M, K, generator=g, device=DEV)
