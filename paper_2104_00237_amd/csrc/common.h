@@ -354,8 +354,8 @@ hipError_t split_launch_conv(int kind, int tile, int S, int cz, int r_split, con
                              hipStream_t stream);
 // bf16-operand contractions (operands rounded to bf16, fp32 accumulation);
 // kinds EPI_FWD, EPI_DGRAD, EPI_WGRAD, EPI_WGRAD_BF; strided operands only.
-hipError_t gemm_bf16_wide_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, int cz,
-                                 hipStream_t stream);
+hipError_t gemm_bf16_wide_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, int S,
+                                 int r_split, int cz, void* ws, hipStream_t stream);
 hipError_t wgrad_bf16_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, hipStream_t stream);
 size_t gemm_bf16_workspace_bytes(int kind, int P, int Q, int R);
 hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, void* ws,

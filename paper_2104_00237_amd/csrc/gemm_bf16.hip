@@ -482,7 +482,6 @@ static int64_t bntiles(int t, int P, int Q) {
   return (int64_t)((P + kBTileBP[t] - 1) / kBTileBP[t]) * ((Q + kBTileBQ[t] - 1) / kBTileBQ[t]);
 }
 
-constexpr int64_t kWideTiles = 160;   // see wide_ok
 static int64_t tiles256(int P, int Q) { return (int64_t)((P + 255) / 256) * ((Q + 255) / 256); }
 
 // 128x256 eight-wave tiles for large outputs (at least 512 of them) and, in
@@ -493,7 +492,9 @@ static int64_t tiles256(int P, int Q) { return (int64_t)((P + 255) / 256) * ((Q 
 // chunks per split).  Gradients keep whole reductions on the wide tiles:
 // backward-fusion runs them beside each other on two streams, where fewer,
 // split workgroups lose what they gain alone (measured on MI355X).  The eager
-// and backward-fusion weight gradients share this rule.
+// and backward-fusion weight gradients share this rule.  The kernels with direct loads
+// (wide_ok, wgrad_ok) take their calls with the same splits, so results do not
+// depend on the operands' storage and alignment.
 static BCfg bselect_default(int kind, int P, int Q, int R) {
   const int64_t nw = bntiles(BTI_128x256, P, Q);
   const bool wide = nw >= 512 || (kind == EPI_FWD && nw >= 128 && R >= 2048);
@@ -510,10 +511,6 @@ static BCfg bselect_default(int kind, int P, int Q, int R) {
   if (kind == EPI_FWD)
     while (S < 8 && (R + S - 1) / S > 2048) S *= 2;
   S = std::min(S, std::min(8, std::max(1, R / (4 * BR))));
-  // Shapes that the kernels with direct loads take unsplit when the operands'
-  // storage and alignment allow: the same order of sums here, so that results do
-  // not depend on either.
-  if ((kind == EPI_FWD || kind == EPI_DGRAD) && tiles256(P, Q) >= kWideTiles) S = 1;
   int r_split = (((R + S - 1) / S) + BR - 1) / BR * BR;
   S = (R + r_split - 1) / r_split;
   return BCfg{t, S, r_split};
@@ -629,7 +626,8 @@ static int bvec_flags(const GemmProblem& pr, int kind, const EpiArgs& ea, int* v
 
 // Whether the 256x256-tile kernel takes a forward or a data gradient: 16-byte
 // pieces of both operands whole or absent, offsets within a buffer descriptor,
-// and at least 160 tiles of them.
+// and at least 160 tiles of them (where every split comes from the length of the
+// reduction).
 static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_ops) {
   if ((kind != EPI_FWD && kind != EPI_DGRAD) || vec_ops != 3 || !pr.b_bf16) return false;
   for (int64_t ld : {pr.a_sp, pr.b_sq, pr.b_sr, ea.ldo, ea.ldz, ea.ldp, ea.ldr})
@@ -637,7 +635,7 @@ static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_
   if (kind == EPI_DGRAD && (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0 ||
                             (int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31)))
     return false;
-  return tiles256(pr.P, pr.Q) >= kWideTiles;
+  return tiles256(pr.P, pr.Q) >= 160;
 }
 
 // Whether the weight-gradient kernel with direct loads takes a weight gradient:
@@ -686,11 +684,10 @@ hipError_t gemm_bf16_launch(int kind, const GemmProblem& pr_in, const EpiArgs& e
   hipError_t e;
   if (wgrad_ok(kind, pr, ea, vec_ops)) return wgrad_bf16_launch(kind, pr, ea, stream);
   if (wide_ok(kind, pr, ea, vec_ops)) {
-    const int cz = ea.carry.t[0].p.w ? carry_slices(ea.carry, tiles256(pr.P, pr.Q)) : 0;
-    ea.carry.cz = cz;
-    return gemm_bf16_wide_launch(kind, pr, ea, cz, stream);
-  }
-  switch (kind) {
+    if (c.cz) c.cz = carry_slices(ea.carry, tiles256(pr.P, pr.Q));
+    ea.carry.cz = c.cz;
+    e = gemm_bf16_wide_launch(kind, pr, ea, c.S, c.r_split, c.cz, ws, stream);
+  } else switch (kind) {
     case EPI_FWD: e = blaunch_kind<EPI_FWD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
     case EPI_DGRAD: e = blaunch_kind<EPI_DGRAD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;
     case EPI_WGRAD: e = blaunch_kind<EPI_WGRAD>(c, pr, ea, ws, vec_ops, vec_epi, stream); break;

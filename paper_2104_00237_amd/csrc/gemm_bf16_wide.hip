@@ -137,9 +137,10 @@ __device__ __forceinline__ wbf16x8_t frag(const char* lds, int x0, int k, int la
 
 // EPI_FWD (A = X, B = W, both reduction-contiguous) or EPI_DGRAD (A = dZ, B = W
 // output-contiguous).  A32: A is stored as fp32.  ACT: a data gradient's
-// activation derivative (its saved tensor's loads); RES: a residual is added.
+// activation derivative (its saved tensor's loads); RES: a residual is added.  A split
+// forward's workgroups store their sums one after the other in ea.out (dense).
 template <int EPI, bool A32, int ACT, bool RES>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, EpiArgs ea) {
+__global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, EpiArgs ea, int r_split) {
   constexpr bool B_RC = EPI == EPI_FWD;
   __shared__ __attribute__((aligned(1024))) char sa0[OPB], sa1[OPB], sb0[OPB], sb1[OPB];
   if constexpr (EPI == EPI_FWD) {
@@ -155,6 +156,13 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
   xcd_tile(tx, ty);
   const int p0 = tx * BT, q0 = ty * BT;
   const int np = pr.P - p0, nq = pr.Q - q0;
+  if constexpr (EPI == EPI_FWD) {   // this split's part of the reduction
+    const int split = (int)blockIdx.z - ea.carry.cz, rbeg = split * r_split;
+    pr.A = (const float*)((const char*)pr.A + (int64_t)rbeg * (A32 ? 4 : 2));
+    pr.B = (const float*)((const char*)pr.B + (int64_t)rbeg * 2);
+    pr.R = min(r_split, pr.R - rbeg);
+    ea.out += (int64_t)split * pr.P * pr.Q;
+  }
   const int nch = (pr.R + BR - 1) / BR;
   const int64_t lda = pr.a_sp, ldb = B_RC ? pr.b_sq : pr.b_sr;
   const rsrc_t ra = make_rsrc((const char*)pr.A + (int64_t)p0 * lda * (A32 ? 4 : 2));
@@ -642,25 +650,38 @@ hipError_t wgrad_bf16_launch(int kind, const GemmProblem& pr, const EpiArgs& ea,
 }
 
 template <int EPI, bool A32, int ACT>
-static hipError_t launch(const GemmProblem& pr, const EpiArgs& ea, int cz, hipStream_t s) {
-  const dim3 g((pr.P + BT - 1) / BT, (pr.Q + BT - 1) / BT, 1 + cz);
+static hipError_t launch(const GemmProblem& pr, const EpiArgs& ea, int S, int r_split, int cz,
+                         hipStream_t s) {
+  const dim3 g((pr.P + BT - 1) / BT, (pr.Q + BT - 1) / BT, S + cz);
   if (ea.res)
-    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, A32, ACT, true>), g, dim3(256), 0, s, pr, ea);
+    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, A32, ACT, true>), g, dim3(256), 0, s, pr, ea, r_split);
   else
-    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, A32, ACT, false>), g, dim3(256), 0, s, pr, ea);
+    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, A32, ACT, false>), g, dim3(256), 0, s, pr, ea, r_split);
   return hipGetLastError();
 }
 
-hipError_t gemm_bf16_wide_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, int cz,
-                                 hipStream_t s) {
+// S > 1 (a forward only): the sums of each split to ws, [S][P][Q]; the caller adds them.
+hipError_t gemm_bf16_wide_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, int S,
+                                 int r_split, int cz, void* ws, hipStream_t s) {
+  EpiArgs ea = ea_in;
+  if (S > 1) {
+    if (kind != EPI_FWD || ws == nullptr) return hipErrorInvalidValue;
+    ea.out = (float*)ws;
+    ea.ldo = pr.Q;
+    ea.yb = nullptr;
+    ea.z = nullptr;
+    ea.bias = nullptr;
+    ea.res = nullptr;
+    ea.act = OF_ACT_NONE;
+  }
   if (kind == EPI_FWD)   // (the forward's activation needs no loads: chosen in the kernel)
-    return pr.a_bf16 ? launch<EPI_FWD, false, OF_ACT_NONE>(pr, ea, cz, s)
-                     : launch<EPI_FWD, true, OF_ACT_NONE>(pr, ea, cz, s);
+    return pr.a_bf16 ? launch<EPI_FWD, false, OF_ACT_NONE>(pr, ea, S, r_split, cz, s)
+                     : launch<EPI_FWD, true, OF_ACT_NONE>(pr, ea, S, r_split, cz, s);
   if (kind != EPI_DGRAD) return hipErrorInvalidValue;
   switch (ea.act) {
-    case OF_ACT_RELU: return launch<EPI_DGRAD, true, OF_ACT_RELU>(pr, ea, cz, s);
-    case OF_ACT_GELU: return launch<EPI_DGRAD, true, OF_ACT_GELU>(pr, ea, cz, s);
-    default: return launch<EPI_DGRAD, true, OF_ACT_NONE>(pr, ea, cz, s);
+    case OF_ACT_RELU: return launch<EPI_DGRAD, true, OF_ACT_RELU>(pr, ea, S, r_split, cz, s);
+    case OF_ACT_GELU: return launch<EPI_DGRAD, true, OF_ACT_GELU>(pr, ea, S, r_split, cz, s);
+    default: return launch<EPI_DGRAD, true, OF_ACT_NONE>(pr, ea, S, r_split, cz, s);
   }
 }
 
