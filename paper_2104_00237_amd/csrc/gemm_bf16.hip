@@ -628,6 +628,13 @@ static int bvec_flags(const GemmProblem& pr, int kind, const EpiArgs& ea, int* v
 // pieces of both operands whole or absent, offsets within a buffer descriptor,
 // and at least 160 tiles of them (where every split comes from the length of the
 // reduction).
+//
+// Its epilogue stores 128-byte row segments from the accumulators.  Where rows are
+// not whole 128-byte lines, the general kernel's longer ones win until the main loop
+// hides that: with Y and Z in fp32 below 1024 reduction elements (4100 x 64 -> 2600
+// with GELU 32 us, 54 here; x 640 66, 68; x 1000 97, 83), in a forward of one fp32 output with
+// whole float4s below 128 (x 64 25.6, 27.1; x 200 32.7, 32.0), and in a data gradient
+// that reads nothing else below 384 (4200 x 200 -> 2568 27.4, 30.7; x 400 38.2, 37.4).
 static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_ops) {
   if ((kind != EPI_FWD && kind != EPI_DGRAD) || vec_ops != 3 || !pr.b_bf16) return false;
   for (int64_t ld : {pr.a_sp, pr.b_sq, pr.b_sr, ea.ldo, ea.ldz, ea.ldp, ea.ldr})
@@ -635,6 +642,10 @@ static bool wide_ok(int kind, const GemmProblem& pr, const EpiArgs& ea, int vec_
   if (kind == EPI_DGRAD && (!aligned16(pr.B) || pr.b_sr % 8 != 0 || pr.Q % 8 != 0 ||
                             (int64_t)pr.R * pr.b_sr * 2 >= (1LL << 31)))
     return false;
+  if (ea.ldo % 32 != 0 || (ea.z && ea.ldz % 32 != 0)) {
+    if (kind == EPI_FWD && !ea.yb && pr.R < (ea.z ? 1024 : ea.ldo % 4 == 0 ? 128 : 0)) return false;
+    if (kind == EPI_DGRAD && ea.act == OF_ACT_NONE && !ea.res && pr.R < 384) return false;
+  }
   return tiles256(pr.P, pr.Q) >= 160;
 }
 

@@ -30,8 +30,10 @@ def _bound(a, b, r):
     return (a.abs() @ b.abs()) * ((r / 8 + 8) * 2.0 ** -24) + 1e-6
 
 
-# at least 160 tiles of 256 x 256; one chunk, a partial one, an odd and an even number of them
-@pytest.mark.parametrize("M,N,K", [(3600, 2600, 64), (3601, 2601, 72), (3841, 2820, 200), (2561, 4098, 256)])
+# at least 160 tiles of 256 x 256; one chunk, a partial one, an odd and an even number of them; rows of
+# whole 128-byte lines and others, where a short reduction with plain fp32 outputs takes the general kernel
+@pytest.mark.parametrize("M,N,K", [(3600, 2600, 64), (3601, 2601, 72), (3841, 2820, 200), (2561, 4098, 256),
+                                   (3601, 2592, 72), (2561, 4128, 200), (2561, 4098, 1032), (3841, 2820, 1024)])
 @pytest.mark.parametrize("x16,y16,act,res", [(1, 1, "gelu", 0), (0, 0, "relu", 1), (1, 0, "none", 1)])
 def test_forward(M, N, K, x16, y16, act, res):
     g = torch.Generator(device=DEV).manual_seed(M + K)
@@ -60,7 +62,8 @@ def test_forward(M, N, K, x16, y16, act, res):
     assert (y.double() - yr).abs().le(1.13 * bound + (zr.abs() + yr.abs()) * 2.0 ** -22 + slack).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(3600, 64, 2600), (3601, 76, 2608), (3841, 200, 2824), (2561, 256, 4104)])
+@pytest.mark.parametrize("M,N,K", [(3600, 64, 2600), (3601, 76, 2608), (3841, 200, 2824), (2561, 256, 4104),
+                                   (3601, 76, 2592), (2561, 200, 4128), (3601, 388, 2608)])
 @pytest.mark.parametrize("act,res", [("none", 0), ("gelu", 0), ("relu", 1), ("none", 1), ("gelu", 1)])
 def test_data_gradient(M, N, K, act, res):
     g = torch.Generator(device=DEV).manual_seed(N + K)
