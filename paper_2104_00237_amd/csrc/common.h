@@ -340,10 +340,10 @@ struct EpiArgs {
 size_t gemm_workspace_bytes(int kind, int P, int Q, int R, int conv = 0);
 hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, void* ws,
                        hipStream_t stream);
-// Tall fp32 products with a short reduction: whether gemm_rows_launch takes one
+// Forwards of tall fp32 products with a short reduction: whether gemm_rows_launch takes one
 // (the same bits as the tiled kernels; no workspace), and its launch.
 bool gemm_rows_ok(int kind, const GemmProblem& pr, const EpiArgs& ea);
-hipError_t gemm_rows_launch(int kind, const GemmProblem& pr, const EpiArgs& ea, hipStream_t stream);
+hipError_t gemm_rows_launch(const GemmProblem& pr, const EpiArgs& ea, hipStream_t stream);
 // The fp32 contractions that run on the bf16 matrix cores (exact three-way
 // operand splits); tile, splits and workspace are gemm_launch's choice.
 hipError_t split_launch_linear(int kind, int tile, int S, int cz, int r_split, const GemmProblem& pr,

@@ -1034,7 +1034,7 @@ static int vec_flags(const GemmProblem& pr, int kind, const EpiArgs& ea, int* ve
 
 hipError_t gemm_launch(int kind, const GemmProblem& pr, const EpiArgs& ea_in, void* ws,
                        hipStream_t stream) {
-  if (gemm_rows_ok(kind, pr, ea_in)) return gemm_rows_launch(kind, pr, ea_in, stream);
+  if (gemm_rows_ok(kind, pr, ea_in)) return gemm_rows_launch(pr, ea_in, stream);
   GemmCfg c = select_cfg(kind, pr.P, pr.Q, pr.R, pr.conv);
   // The 128x128 tile leaves no LDS for forward-fusion's bias row; a fused
   // forward given it takes 128x64 with the same splits (the same reduction
