@@ -310,11 +310,8 @@ __device__ __forceinline__ float4 dwv_dact(float4 acc, int act, const float* p, 
   return make_float4(__fmul_rn(acc.x, act_grad(act, v.x)), __fmul_rn(acc.y, act_grad(act, v.y)),
                      __fmul_rn(acc.z, act_grad(act, v.z)), __fmul_rn(acc.w, act_grad(act, v.w)));
 }
-__device__ __forceinline__ void dwv_store(float* p, float v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void dwv_store(float* p, float4 v) {
-  typedef float f4 __attribute__((ext_vector_type(4)));
-  __builtin_nontemporal_store(f4{v.x, v.y, v.z, v.w}, reinterpret_cast<f4*>(p));
-}
+__device__ __forceinline__ void dwv_store(float* p, float v) { *p = v; }
+__device__ __forceinline__ void dwv_store(float* p, float4 v) { st4(p, v); }
 
 template <int S, class V>
 __global__ __launch_bounds__(256) void dw_fwd_sweep_kernel(const float* __restrict__ x,
