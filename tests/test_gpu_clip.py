@@ -95,6 +95,20 @@ def test_clip_scale_matches_oracle(env, case):
     assert s == 1.0
 
 
+@pytest.mark.parametrize("n", [(1 << 20) + 3, (3 << 20) + 1, (4 << 20) + 2, (8 << 20) + (1 << 18) + 3])
+def test_clip_scale_long(env, n):
+    """Past one step of the grid (2^20 elements) and past its four loads in flight: every step of 2^20
+    elements has a magnitude of its own, so that one left out or counted twice shows."""
+    torch, L, dev = env
+    r = np.random.default_rng(n)
+    a = r.standard_normal(n).astype(np.float32) * np.float32(1.3) ** (np.arange(n) >> 20).astype(np.float32)
+    a[-3:] = 5e3      # the last elements past whole float4s
+    ref_s, ref_n = _ref([a], 1.0)
+    s, nn = _clip_gpu(torch, L, dev, [a], 1.0)
+    assert abs(nn - ref_n) <= 1e-6 * ref_n
+    assert abs(s - ref_s) <= 1e-6 * ref_s
+
+
 def test_clip_scale_non_finite(env):
     torch, L, dev = env
     a = np.ones(100, np.float32)
