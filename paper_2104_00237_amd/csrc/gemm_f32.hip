@@ -52,14 +52,9 @@ namespace opfuse {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-template <int BP_, int BQ_, int BR_, int WP_, int WQ_, int WR_, int NS_, int PAD_ = 4>
+template <int BP_, int BQ_, int BR_, int WP_, int WQ_, int WR_, int NS_>
 struct Tile {
   static constexpr int BP = BP_, BQ = BQ_, BR = BR_, WP = WP_, WQ = WQ_, WR = WR_;
-  // LDS row padding of the operand tiles (floats).  4 keeps rows 16-byte
-  // aligned for the vector stores of output-contiguous operands; a tile whose
-  // operands are both reduction-contiguous (stored one float at a time) may
-  // take 2, which spreads its transposing stores over all 64 banks.
-  static constexpr int PAD = PAD_;
   static constexpr int NS = NS_;  // operand chunks in the register ring
   static_assert(WP * WQ * WR == 4, "a workgroup is 4 wavefronts");
   static constexpr int WTP = BP / WP, WTQ = BQ / WQ;   // wavefront tile
@@ -67,7 +62,7 @@ struct Tile {
   static_assert(TP >= 1 && TQ >= 1 && WTP % 32 == 0 && WTQ % 32 == 0, "32x32 blocks");
   static constexpr int RW = BR / WR;                    // chunk rows per wavefront
   static_assert(RW % 2 == 0 && BR % 4 == 0, "k pairs");
-  static constexpr int LDA = BP + PAD, LDB = BQ + PAD;
+  static constexpr int LDA = BP + 4, LDB = BQ + 4;   // LDS rows, 16-byte aligned
   static constexpr int LDC = (WR * BP * (BQ + 4) * 4 <= 60 * 1024) ? BQ + 4 : BQ;
   static constexpr int SM_MAIN = 2 * BR * (LDA + LDB);
   static constexpr int SM_C = WR * BP * LDC;
@@ -108,7 +103,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmProblem pr, EpiArgs ea, i
   // Forward-fusion also keeps the updated bias slice of its column tile.
   constexpr int SMEM = T::SMX + (EPI == EPI_FWD_FF ? T::BQ : 0);
   static_assert(SMEM * 4 <= 160 * 1024, "LDS per workgroup");
-  static_assert(EPI != EPI_FWD_FF || T::PAD == 4, "the fused forward stages W with a pad of 4");
   __shared__ __attribute__((aligned(16))) float smem[SMEM];
   if constexpr (EPI == EPI_FWD) {
     if ((int)blockIdx.z < ea.carry.cz) {
@@ -193,11 +187,11 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmProblem pr, EpiArgs ea, i
   using ALoad = std::conditional_t<
       CONV && (EPI == EPI_FWD || EPI == EPI_FWD_FF || EPI == EPI_DGRAD),
       GatherLoad<T::BP, T::BR, true, VA, EPI == EPI_DGRAD ? G_DGRAD_A : G_FWD_A>,
-      TileLoad<T::BP, T::BR, A_RC, VA, T::PAD>>;
+      TileLoad<T::BP, T::BR, A_RC, VA>>;
   using BLoad = std::conditional_t<
       CONV && EPI == EPI_DGRAD, GatherLoad<T::BQ, T::BR, false, VB, G_DGRAD_B>,
       std::conditional_t<CONV && WG, GatherLoad<T::BQ, T::BR, false, VB, G_WGRAD_B>,
-                         TileLoad<T::BQ, T::BR, B_RC, VB, T::PAD>>>;
+                         TileLoad<T::BQ, T::BR, B_RC, VB>>>;
   ALoad la[NS];
   BLoad lb[(EPI == EPI_FWD_FF) ? 1 : NS];
   FFTileLoad<T::BQ, T::BR, VB> lf[(EPI == EPI_FWD_FF) ? NS : 1];

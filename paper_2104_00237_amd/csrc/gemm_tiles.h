@@ -13,7 +13,7 @@ namespace opfuse {
 // tile's first element; nx / nr are the valid extents from there (<= 0: none).
 // vec: 128-bit loads (base 16B aligned, strides and both extents' ends
 // multiples of 4 along the contiguous index).
-template <int BX, int BR, bool RC, bool VEC, int PAD = 4>
+template <int BX, int BR, bool RC, bool VEC>
 struct TileLoad {
   static constexpr int NV = BX * BR / 4;
   static constexpr int PER = (NV + 255) / 256;
@@ -47,8 +47,7 @@ struct TileLoad {
   }
 
   __device__ __forceinline__ void store(float* lds, int tid) const {
-    constexpr int LD = BX + PAD;
-    static_assert(RC || PAD % 4 == 0, "float4 stores need 16-byte aligned rows");
+    constexpr int LD = BX + 4;   // rows stay 16-byte aligned
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int idx = tid + i * 256;
