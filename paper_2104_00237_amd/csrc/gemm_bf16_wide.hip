@@ -16,11 +16,10 @@
 // during steps 0..2 of the chunk after its loads were issued).  The two buffers are
 // arrays of their own: the compiler then knows which reads a load to LDS concerns.
 //
-// Measured: the main loop at 1.45 PFLOP/s; 4096 x 4096 x 1024 forward with GELU, Z and a
-// bf16 Y 83 -> 57 us (100 MB of stores: staged through LDS they took 55 us of a
-// plain forward's 79, from the accumulators about 30); its data gradient with
-// GELU's derivative (4096 x 1024 x 4096) 95 -> 63 us.  Below 160 tiles the chip is
-// not full and the general kernel's smaller tiles win.
+// Measured: 4096 x 4096 x 1024 forward with GELU, Z and a bf16 Y 75 -> 58 us (100 MB of
+// stores; the MFMAs are a fifth of it); a data gradient of that size with GELU's
+// derivative 93 -> 55.  Below 160 tiles the chip is not full and the general kernel's
+// smaller tiles win.  A long forward is split as there (4096 x 4096 x 8192 395 -> 360 us).
 //
 // LDS layout: reduction-contiguous operands as rows [x][64], 16-byte slots
 // XOR-swizzled by (x >> 1) & 7, so 16 consecutive rows' reads cover all banks;
@@ -393,9 +392,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(GemmProblem pr, 
 // contiguous: dZ (fp32) through registers, X (bf16) straight to LDS, both read with
 // ds_read_b64_tr_b16; the main loop is the one above with 64x64 sub-tiles.  The
 // update runs on the accumulators: W, m and v are requested a 32x32 block ahead
-// and moved in 128-byte row segments.  Bound by LDS and the loads (768 clocks of
-// either per chunk, 512 of MFMAs), then by the update's memory traffic.
-// 1024 x 4096 over 4096 rows with AdamW: backward and update 173 -> 154.5 us.
+// and moved in 128-byte row segments.  Bound by LDS and the loads (by count 768 clocks
+// of either per chunk, 512 of MFMAs), then by the update's memory traffic: 1024 x 4096
+// over 4096 rows with AdamW 95 -> 78 us, the plain gradient 80 -> 55.
 namespace {
 
 constexpr int WT = 128;                  // tile rows and columns

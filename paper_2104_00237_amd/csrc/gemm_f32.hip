@@ -748,8 +748,9 @@ static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {
     GemmCfg c = make_cfg(ff_tile(P), P, Q, R, 1024, 8);
     // Between 33 and 64 rows, with enough columns to fill the chip: 64x128
     // tiles on the bf16 matrix cores with the same splits (measured on MI355X at
-    // 64 x 8192 x 8192: 62 us, 82 us on fp32 tiles of that size); the fused
-    // forward of that shape takes 64x32 tiles of the same reduction layout.
+    // 64 x 8192 x 8192 with the second pass: 80 to 83 us alone, 80 to 84 on fp32 tiles of
+    // that size; in a step of four such layers an eighth less); the fused forward of
+    // that shape takes 64x32 tiles of the same reduction layout.
     if (P > 32 && ntiles(TI_S64x128, P, Q) * c.S >= 256) c.tile = TI_S64x128;
     return c;
   }
