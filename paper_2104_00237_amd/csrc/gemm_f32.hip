@@ -717,22 +717,38 @@ static GemmCfg cheapest_split(int kind, int P, int Q, int R, int conv) {
 // 1024 x 1024 18.1 / 18.6, 1024 x 1024 x 1024 28 / 25, 1024 x 2048 x 2048 79 / 66; data
 // gradient 512 x 1024 x 1024 15.6 / 18.6, 2048 x 512 x 768 22.1 / 18.9, 1024 x 2048 x 2048
 // 78 / 69; weight gradient 512 x 1024 x 1024 18.0 / 14.1 (fused 20.2 / 19.2), 1024 x 2048 x
-// 2048 84 / 70 (95 / 80).  A reduction split in two pays later (forward 640 x 1000 x 1004
-// 20.2 / 22.7), a data gradient on few tiles too (768 x 1024 x 1024 21.4 / 22.8), and so do a data gradient of
-// at most 64 rows (64 x 4096 x 4096 26.0 / 27.4; 40 x 4096 x 8192 41.5 / 38.8) and a weight
-// gradient with single loads over a short reduction (577 x 1033 x 1031 34.8 / 38.7,
-// 900 x 1033 x 1031 52 / 48; 1001 x 801 x 903 38 / 34).
+// 2048 84 / 70 (95 / 80).  What loses, from 450 sizes of 0.6 to 9.5 GFLOP (rows, outputs,
+// inputs; below, the contraction's own P x Q x R):
+//   a forward split in two (512 x 1277 x 2000 36.0 / 39.1, 1698 x 344 x 2104 wins by 11%) and a
+//   data gradient on few tiles (768 x 1024 x 1024 21.4 / 22.8) until later;
+//   a data gradient of at most 64 rows (64 x 4096 x 4096 26.0 / 27.4; 40 x 4096 x 8192 41.5 / 38.8);
+//   a data gradient with single loads of W alone, where the fp32 tiles are the 32x32
+//   ones that load straight to registers (375 x 1302 x 5304 72 / 110, 1132 x 491 x 4064 72 / 101);
+//   a weight gradient with single loads over a short reduction (577 x 1033 x 1031 34.8 / 38.7,
+//   900 x 1033 x 1031 52 / 48; 1001 x 801 x 903 38 / 34), or over at most 128 rows in 4 to 8
+//   rounds of 256 tiles (64 x 4089 x 4160 46 / 39, but fused 77 / 139), on fewer workgroups than CUs or
+//   split, below 1000 rows (1424 x 528 x 993 20.8 / 25.0, 440 x 1000 x 976 14.7 / 18.0), and one that
+//   a few workgroups keep from ending in one round of 256 (504 x 2108 x 945 27.6 / 30.7; in
+//   two splits when these are long, 672 x 912 x 5439 73.8 / 87.6).
 static bool split_pays(int kind, int P, int Q, int R, const GemmCfg& c) {
   const double flops = 2.0 * P * Q * R;
   if (P <= 32 || Q <= 32 || R < 64) return false;
   if (kind == EPI_WGRAD || kind == EPI_WGRAD_BF) {
-    const bool vec = P % 4 == 0 && Q % 4 == 0;
-    return flops >= (!vec && R <= 1000 ? 1.6e9 : 8e8);
+    const int64_t wgs = ntiles(c.tile, P, Q) * c.S;
+    if (P % 4 != 0 || Q % 4 != 0) {
+      if (R <= 128 && wgs >= 1024 && wgs < 2048) return false;
+      return flops >= (R <= 1000 ? 1.6e9 : 8e8);
+    }
+    if (R < 1000 && (c.S > 1 || wgs <= 210)) return false;
+    if (wgs > 256 && (c.S == 1 ? wgs <= 310 : c.S == 2 && wgs <= 340 && R >= 3400)) return false;
+    return flops >= 8e8;
   }
-  if (kind == EPI_DGRAD && P <= 64) return flops >= 2.5e9;
-  if (c.S == 2 || (kind == EPI_DGRAD && c.S == 1 && ntiles(c.tile, P, Q) < 224))
-    return flops >= (kind == EPI_DGRAD ? 1.7e9 : 1.3e9);
-  return flops >= 1.2e9;
+  if (kind == EPI_DGRAD) {
+    if (P <= 64) return flops >= 2.5e9;
+    if (R % 4 == 0 && Q % 4 != 0 && ntiles(TI_64x64, P, Q) < 256) return false;
+    return flops >= (c.S == 2 || (c.S == 1 && ntiles(c.tile, P, Q) < 224) ? 1.7e9 : 1.2e9);
+  }
+  return flops >= (c.S == 2 ? (R % 4 == 0 ? 2.7e9 : 1.3e9) : 1.2e9);
 }
 
 static GemmCfg select_cfg_default(int kind, int P, int Q, int R) {

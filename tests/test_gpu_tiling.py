@@ -135,3 +135,38 @@ def test_bf16_long_forward(M, N, K, x16, y16, act, res):
     ref = x[:n].bfloat16().double() @ wb.double().t() + b.double()
     err = ((outs[0][1][:n].double() - ref).norm() / ref.norm()).item()
     assert err <= 3.2e-7, err
+
+
+# sizes on the fp32 tiles again, beside ones like them on the bf16 matrix cores: a short weight gradient on
+# few workgroups, split, just past one round of 256, past it in two splits, with single loads over few rows;
+# a data gradient with single loads of W alone; a forward split in two
+@pytest.mark.parametrize("M,N,K", [(993, 1424, 528), (1001, 1424, 528), (976, 440, 1000), (945, 504, 2108),
+                                   (945, 504, 2560), (5439, 672, 912), (3390, 672, 912), (64, 4089, 4160),
+                                   (375, 5304, 1302), (375, 5303, 1302), (512, 1277, 2000), (512, 1277, 2100)])
+def test_fp32_rules(M, N, K):
+    """Forward and gradients against float64 (at most r roundings of sum |ab|; the fp32 tiles' chains hold r / 2
+    products), and the fused update bit for bit against the eager gradient and step."""
+    g, s = torch.Generator(device=DEV).manual_seed(M + N + K), _stream()
+    x, w, dz = (torch.randn(*n, generator=g, device=DEV) for n in ((M, K), (N, K), (M, N)))
+    y, dx, dw = torch.empty(M, N, device=DEV), torch.empty(M, K, device=DEV), torch.empty(N, K, device=DEV)
+    d = L.OfLinearDesc(M, N, K, 0, 0, L.OF_F32, L.OF_ACT_NONE, 0, 0)
+    keep, ws = _ws(max(L.of_linear_workspace_size(d, o) for o in (0, 1, 2)))
+    W = L.OfParam(w.data_ptr(), None, None, None, w.numel())
+    L.of_linear_fwd(d, x.data_ptr(), W, None, None, y.data_ptr(), *ws, s)
+    L.of_linear_bwd_data(d, dz.data_ptr(), W, None, 0, dx.data_ptr(), *ws, s)
+    L.of_linear_bwd_weight(d, dz.data_ptr(), x.data_ptr(), dw.data_ptr(), None, 0, *ws, s)
+    x64, w64, z64 = x.double(), w.double(), dz.double()
+    for out, a, b, r in ((y, x64, w64.t(), K), (dx, z64, w64, N), (dw, z64.t(), x64, M)):
+        bound = (a.abs() @ b.abs()) * (r * 2.0 ** -24)
+        assert (out.double() - a @ b).abs().le(bound).all()
+    o = L.make_opt(dict(kind="adam", lr=1e-2, beta1=0.9, beta2=0.99, eps=1e-8, weight_decay=0.0), 2)
+    sets = []
+    for _ in range(2):
+        h = torch.Generator(device=DEV).manual_seed(3)
+        sets.append([torch.rand(N * K, generator=h, device=DEV) for _ in range(3)])
+    P = L.param_of(*sets[0])
+    L.of_optimizer_step(1, (L.OfParam * 1)(P), (L.c_void_p * 1)(dw.data_ptr()), o, s)
+    L.of_linear_bwd_fused(d, dz.data_ptr(), x.data_ptr(), L.param_of(*sets[1]), None, None, None, o, None, 0, None,
+                          None, 0, *ws, s, None)
+    for p, q in zip(*sets):
+        assert torch.equal(p, q)
