@@ -310,6 +310,9 @@ __device__ __forceinline__ float4 dwv_dact(float4 acc, int act, const float* p, 
   return make_float4(__fmul_rn(acc.x, act_grad(act, v.x)), __fmul_rn(acc.y, act_grad(act, v.y)),
                      __fmul_rn(acc.z, act_grad(act, v.z)), __fmul_rn(acc.w, act_grad(act, v.w)));
 }
+// (through the caches: the next layer reads the output at once.  Stores that bypass them
+// gain 3% here alone, 137 -> 132 us for 32 x 56 x 56 x 144 with its backward, and cost
+// MobileNetV2's step 0.6%, 3.00 -> 3.02 ms.)
 __device__ __forceinline__ void dwv_store(float* p, float v) { *p = v; }
 __device__ __forceinline__ void dwv_store(float* p, float4 v) { st4(p, v); }
 
