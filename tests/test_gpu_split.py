@@ -135,7 +135,8 @@ def test_one_product(M, N, K):
 
 
 @pytest.mark.parametrize("N,H,Wd,C,Co", [(64, 9, 12, 96, 160), (16, 15, 15, 256, 256), (64, 9, 12, 99, 100),
-                                         (9, 15, 15, 254, 256), (64, 9, 12, 100, 99)])
+                                         (9, 15, 15, 254, 256), (64, 9, 12, 100, 99),
+                                         (12, 15, 15, 254, 256), (64, 9, 12, 150, 150)])
 def test_one_product_conv(N, H, Wd, C, Co):
     g = torch.Generator(device=DEV).manual_seed(C + Co)
     M = N * H * Wd
