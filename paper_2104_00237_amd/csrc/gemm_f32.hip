@@ -847,15 +847,16 @@ static GemmCfg select_cfg_conv(int kind, int P, int Q, int R) {
   // bf16 matrix cores, forward, data and weight gradient: 128 x 8 x 8 x 256 -> 256
   // 97 / 76, 103 / 76, 105 / 92 us; 16 x 14 x 14 x 96 -> 160 23 / 19, 25 / 20, 23 / 20).
   // Not over fewer than 600 pixels in a weight gradient (28 x 4 x 5 x 112 -> 456 12.1 / 15.9) and not
-  // below 3 GFLOP in a forward of at most 16 channels (32 x 28 x 28 x 9 -> 160 33 / 40, 57024 pixels of
-  // 14 -> 448, 6.4 GFLOP, gain 45%).  A weight gradient that gathers single channels (C % 4
+  // below 3 GFLOP over at most 144 reduction elements (16 channels): 43 x 28 x 28 x 9 -> 160
+  // forward 33 / 40, 44 x 16 x 16 x 216 -> 16 data gradient 15.1 / 16.4 (57024 pixels of 14 -> 448,
+  // 6.4 GFLOP, gain 45%).  A weight gradient that gathers single channels (C % 4
   // != 0, Q = 9 C) does so for every 64 output channels there: from 2.5 GFLOP (12 x 16 x 17 x 149
   // -> 72, 0.6, 28 / 37; 64 x 15 x 16 x 99 -> 100, 2.7, 57 / 50) to 4 (128 x 8 x 8 x 255 -> 257 182 /
   // 184, x 254 -> 256 137 / 131).
   const bool wg = kind == EPI_WGRAD || kind == EPI_WGRAD_BF;
   const double flops = 2.0 * P * Q * R;
   const bool pays = wg ? (Q % 4 == 0 ? R >= 600 && flops >= 5e8 : flops >= 2.5e9 && flops < 4e9)
-                       : flops >= (kind != EPI_DGRAD && R <= 144 ? 3e9 : 5e8);
+                       : flops >= (R <= 144 ? 3e9 : 5e8);
   if (P > 32 && Q > 32 && R >= 64 && pays) return cheapest_split(kind, P, Q, R, 1);
   static const double kEff[6] = {0.489, 0.283, 0.617, 0.488, 0.714, 0.765};
   static const int kConc[6] = {1, 4, 3, 4, 2, 1};
